@@ -10,7 +10,8 @@
  * integer matrix product (Sec. 2.2: one operand becomes the negacyclic
  * Toeplitz matrix of Eq. (3)), split into balanced signed 8-bit limbs
  * (Sec. 2.4, strategy (ii): several small units per coefficient) and tiled
- * over the degree (Sec. 2.5, divide and conquer).
+ * over the degree (Sec. 2.5, divide and conquer); where it pays, the product is
+ * first cut into shorter negacyclic products by a polynomial transform.
  *
  * Conventions shared by every entry point:
  *   - Polynomials are stored lowest degree first, one machine word per
@@ -265,7 +266,8 @@ polymul_status polymul_negacyclic_rns_karatsuba_noalloc(const uint32_t* a, const
  * cut into (n = t * r): n itself when n <= 32, otherwise a power of two in
  * [32, min(n, 128)] (32x32 output tiles, v_mfma_i32_32x32x32_i8), or 16 for
  * 64 <= n <= 512 (16x16 output tiles, v_mfma_i32_16x16x64_i8, the built-in
- * choice there).  t = 0 restores the built-in choice.  The table is
+ * choice there).  t = 0 restores the built-in choice, which for n = 1024..4096 and
+ * odd moduli is the polynomial transform instead of tiles of the whole product.  The table is
  * process-wide; the autotuner (paper_2307_06554_amd/tune.py) times the
  * candidates on the GPU and calls polymul_tune_set with the winners.  Takes
  * effect for launches and plans created afterwards.  No HIP call is made.

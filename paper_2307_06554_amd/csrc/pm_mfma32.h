@@ -366,7 +366,8 @@ struct GroupInfo {
   uint32_t li[4];     // modulus index of each staged slot
 };
 
-__device__ __forceinline__ uint64_t global_product(const Mfma32Params& P, uint64_t prod, uint32_t* li) {
+template <typename Params>
+__device__ __forceinline__ uint64_t global_product(const Params& P, uint64_t prod, uint32_t* li) {
   if ((prod >> 32) == 0) {  // 32-bit quotients (the usual case) are much cheaper
     const uint32_t p32 = (uint32_t)prod;
     if (P.lrep > 1) {
@@ -386,7 +387,8 @@ __device__ __forceinline__ uint64_t global_product(const Mfma32Params& P, uint64
 }
 
 // Product whose b a staged product uses: its own, or its channel's shared one.
-__device__ __forceinline__ uint64_t b_product(const Mfma32Params& P, uint64_t gp, uint32_t li) {
+template <typename Params>
+__device__ __forceinline__ uint64_t b_product(const Params& P, uint64_t gp, uint32_t li) {
   return P.b_shared ? (uint64_t)(P.l0 + li) : gp;
 }
 

@@ -12,6 +12,7 @@
 #include "pm_common.h"
 #include "pm_mfma32.h"
 #include "pm_mfma16.h"
+#include "pm_ptrans.h"
 #include "pm_plain.h"
 #include "pm_stream.h"
 #include "pm_grouped.h"
@@ -281,6 +282,7 @@ template <int L, typename W, int WPE> const void* k_stream() { return (const voi
 template <typename W> const void* k_stream8() { return (const void*)stream8_kernel<W>; }
 const void* k_grouped() { return (const void*)grouped_kernel; }
 template <int L> const void* k_shared() { return (const void*)mfma32_shared_kernel<L>; }
+template <int L, int LK> const void* k_ptrans() { return (const void*)ptrans_kernel<L, LK>; }
 template <int L, bool SHB> const void* k_small() { return (const void*)mfma16_group_kernel<L, SHB>; }
 
 template <int L, bool SMALL>
@@ -571,6 +573,70 @@ polymul_status run_stream(const W* a, const W* b, W* c, uint32_t n, const uint64
   return POLYMUL_EINVAL;
 }
 
+// ----------------------------------------------------- polynomial transform
+// Moduli the transform takes: odd (2k and the Montgomery step need an inverse) and with
+// room for a sum of two residues in a word that the digit window covers as it is.
+bool ptrans_modulus(uint32_t q) { return (q & 1) && q >= 3 && q <= (uint32_t)limb_top(4); }
+
+void fill_ptmod(PtMod& pm, uint32_t q, int L, uint32_t points) {
+  pm = PtMod{};
+  pm.m = make_mod32(q, L);
+  uint32_t inv = q;  // Newton: doubles the correct low bits, three to begin with
+  for (int i = 0; i < 5; ++i) inv *= 2 - q * inv;
+  pm.qinv = inv;
+  pm.lift = (uint64_t)q * ((uint64_t)L * L * kPtM << 13);
+  // 2^32 / points mod q, halving with the odd q
+  uint64_t f = ((uint64_t)1 << 32) % q;
+  for (uint32_t p = points; p > 1; p /= 2) f = f & 1 ? (f + q) / 2 : f / 2;
+  for (int s = 0; s < 2 * L - 1; ++s) {
+    pm.rc[s] = f > q / 2 ? (int32_t)((int64_t)f - q) : (int32_t)f;
+    f = (f << 8) % q;
+  }
+}
+
+template <int L, int LK>
+polymul_status launch_ptrans(const PtParams& P, hipStream_t s) {
+  if (allow_lds<k_ptrans<L, LK>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
+  constexpr uint32_t G = 16 >> LK;
+  const uint64_t groups = (P.nprod + G - 1) / G;
+  if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
+  hipLaunchKernelGGL((ptrans_kernel<L, LK>), dim3((uint32_t)groups), dim3(kThreads), pt_lds_bytes<L>(), s, P);
+  return launch_status();
+}
+template <int L>
+polymul_status launch_ptrans_L(const PtParams& P, hipStream_t s) {
+  switch (P.n) {
+    case 1024: return launch_ptrans<L, 2>(P, s);
+    case 2048: return launch_ptrans<L, 3>(P, s);
+    default: return launch_ptrans<L, 4>(P, s);
+  }
+}
+
+bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L) {
+  if (n < 1024 || n > 4096) return false;
+  if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;  // a tile side was asked for
+  for (uint32_t i = 0; i < lc; ++i)
+    if (!ptrans_modulus(qs[i])) return false;
+  return true;
+}
+
+polymul_status run_ptrans(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
+                          uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, hipStream_t s,
+                          uint32_t lrep, bool b_shared) {
+  PtParams P{};
+  P.a = a; P.b = b; P.c = c;
+  P.nprod = nprod;
+  P.n = n;
+  P.lc = lc; P.nq_total = nq_total; P.l0 = l0; P.lrep = lrep;
+  P.b_shared = b_shared ? 1u : 0u;
+  for (uint32_t i = 0; i < lc; ++i) fill_ptmod(P.mods[i], qs[i], L, 2 * n / kPtM);
+  switch (L) {
+    case 2: return launch_ptrans_L<2>(P, s);
+    case 3: return launch_ptrans_L<3>(P, s);
+    default: return launch_ptrans_L<4>(P, s);
+  }
+}
+
 // nprod products (i -> global (i/lc)*nq_total + l0 + i%lc) with moduli qs[0..lc <= kMaxQ).
 polymul_status run_mfma32(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
                           uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, hipStream_t s,
@@ -596,6 +662,8 @@ polymul_status run_mfma32(const uint32_t* a, const uint32_t* b, uint32_t* c, uin
     return POLYMUL_OK;
   }
   const int L = limbs32(qs, lc);
+  if (!cyclic && ptrans_takes(n, qs, lc, L))
+    return run_ptrans(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s, lrep, b_shared);
   Mfma32Params P;
   uint32_t lds;
   polymul_status st =

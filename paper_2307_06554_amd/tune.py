@@ -5,7 +5,8 @@ selection) and names Karatsuba as a further improvement (Sec. 4); here the
 experiments are automated and their winners loaded into the library:
 
   - the Toeplitz tile side t of the resident 32-bit path per degree bound n
-    (16: the 16x16-tile kernel; 32, 64, 128: 32x32 tiles), polymul_tune_set;
+    (16: the 16x16-tile kernel; 32, 64, 128: 32x32 tiles; 0: the library's own
+    choice, which for the degrees it takes is the polynomial transform), polymul_tune_set;
   - the Karatsuba depth per degree bound and batch (the direct route included),
     for 32-bit RNS products and for 64-bit words, polymul_tune_set_karatsuba;
   - the K-run cap of the 64-bit Karatsuba route and the two scheduling knobs of
@@ -107,7 +108,8 @@ def tune_tiles(ns, Ls, work, log):
             products = max(64, min(65536, work // (n * n)))
             a, b = _rand((products, n), q, n), _rand((products, n), q, n + 1)
             c = a.clone()
-            timings = {}
+            # 0: the library's own choice, which is not a tile for every degree
+            timings = {0: time_us(lambda: binding.polymul_negacyclic(a, b, q, out=c))}
             for t in candidates(n):
                 binding.polymul_tune_set(n, L, t)
                 try:
@@ -117,9 +119,7 @@ def tune_tiles(ns, Ls, work, log):
                     continue
                 finally:
                     binding.polymul_tune_set(n, L, 0)
-            if not timings:
-                continue
-            best = pick(timings, binding.polymul_tune_get(n, L))
+            best = pick(timings, 0)
             log(f"tile n={n:6d} L={L} products={products:6d} " +
                 " ".join(f"t={t}:{us:8.1f}us" for t, us in timings.items()) + f"  -> t={best}")
             entries.append({"n": n, "L": L, "t": best, "products": products,
