@@ -207,7 +207,10 @@ polymul_status polymul_negacyclic_u64_shared(const uint64_t* a, const uint64_t* 
  *                for this degree bound and number of products (batch * L):
  *                polymul_tune_set_karatsuba, else a built-in one.  Where that
  *                choice is the direct route (no levels) the call is
- *                polymul_negacyclic_rns and the workspace is not used.
+ *                polymul_negacyclic_rns and the workspace is not used.  Where
+ *                nothing is tuned and n >= 1024, moduli the polynomial transform
+ *                takes (odd, at most 0x7F7F7F7F for 32-bit words) go through it
+ *                instead of Karatsuba levels, in the same workspace.
  *   workspace:   device, 16-byte aligned, at least
  *                polymul_karatsuba_workspace_size(...) bytes, owned by the
  *                caller, not overlapping a, b or c; its contents on entry do

@@ -146,8 +146,11 @@ int ilog2_floor(uint64_t x) {
 // Depth for a call of `products` products of degree bound n: the table's, else the
 // built-in choice (two levels from n = 1024 on, one at 512 for 32-bit words; for
 // 64-bit words three from n = 8192 on, else one), never below n / 2^depth = 4.
+uint32_t kara_tuned(uint64_t n, uint64_t products, bool wide) {
+  return (wide ? g_kara64_depth : g_kara_depth)[ilog2(n)][ilog2_floor(products)].load(std::memory_order_relaxed);
+}
 uint32_t kara_depth_for(uint64_t n, uint64_t products, bool wide) {
-  uint32_t d = (wide ? g_kara64_depth : g_kara_depth)[ilog2(n)][ilog2_floor(products)].load(std::memory_order_relaxed);
+  uint32_t d = kara_tuned(n, products, wide);
   if (d == kNotTuned) d = wide ? (n >= 8192 ? 3 : 1) : (n >= 1024 ? 2 : n >= 512 ? 1 : 0);
   while (d > 0 && (n >> d) < 4) --d;
   return d;
@@ -282,7 +285,7 @@ template <int L, typename W, int WPE> const void* k_stream() { return (const voi
 template <typename W> const void* k_stream8() { return (const void*)stream8_kernel<W>; }
 const void* k_grouped() { return (const void*)grouped_kernel; }
 template <int L> const void* k_shared() { return (const void*)mfma32_shared_kernel<L>; }
-template <int L, int LK> const void* k_ptrans() { return (const void*)ptrans_kernel<L, LK>; }
+template <typename W, int L, int LK> const void* k_ptrans() { return (const void*)ptrans_kernel<W, L, LK>; }
 template <int L, bool SHB> const void* k_small() { return (const void*)mfma16_group_kernel<L, SHB>; }
 
 template <int L, bool SMALL>
@@ -574,12 +577,14 @@ polymul_status run_stream(const W* a, const W* b, W* c, uint32_t n, const uint64
 }
 
 // ----------------------------------------------------- polynomial transform
-// Moduli the transform takes: odd (2k and the Montgomery step need an inverse) and with
-// room for a sum of two residues in a word that the digit window covers as it is.
+// Moduli the transform takes: odd (the points' number and the Montgomery step need
+// inverses); 32-bit words also need room for a sum of two residues in a word that the digit
+// window covers as it is.
 bool ptrans_modulus(uint32_t q) { return (q & 1) && q >= 3 && q <= (uint32_t)limb_top(4); }
 
-void fill_ptmod(PtMod& pm, uint32_t q, int L, uint32_t points) {
-  pm = PtMod{};
+// `points`: the transform's points, the outer one's included (their inverse goes into rc).
+bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points) {
+  pm = PtMod32{};
   pm.m = make_mod32(q, L);
   uint32_t inv = q;  // Newton: doubles the correct low bits, three to begin with
   for (int i = 0; i < 5; ++i) inv *= 2 - q * inv;
@@ -592,29 +597,60 @@ void fill_ptmod(PtMod& pm, uint32_t q, int L, uint32_t points) {
     pm.rc[s] = f > q / 2 ? (int32_t)((int64_t)f - q) : (int32_t)f;
     f = (f << 8) % q;
   }
+  return true;
+}
+// False when a constant of this modulus does not split into two signed words.
+bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {
+  pm = PtMod64{};
+  pm.m = make_mod64(q, L);
+  uint64_t inv = q;
+  for (int i = 0; i < 6; ++i) inv *= 2 - q * inv;
+  pm.qinv = inv;
+  pm.lift0 = (int64_t)((q & 0xFFFFFFFFull) << 28);
+  pm.lift1 = (int64_t)((q >> 32) << 28);
+  typedef unsigned __int128 u128;
+  u128 f = ((u128)1 << 64) % q;
+  for (uint32_t p = points; p > 1; p /= 2) f = f & 1 ? (f + q) / 2 : f / 2;
+  for (int s = 0; s < 2 * L - 1; ++s) {
+    bool fits = false;
+    for (int neg = 0; neg < 2 && !fits; ++neg) {  // the centred residue, else the other one next to it
+      const __int128 w = (f > q / 2) != (neg == 1) ? (__int128)f - q : (__int128)f;
+      const int32_t w0 = (int32_t)(uint32_t)(u128)w;
+      const __int128 w1 = (w - w0) >> 32;
+      if (w1 >= INT32_MIN && w1 <= INT32_MAX) {
+        pm.w0[s] = w0;
+        pm.w1[s] = (int32_t)w1;
+        fits = true;
+      }
+    }
+    if (!fits) return false;
+    f = (f << 8) % q;
+  }
+  return true;
 }
 
-template <int L, int LK>
-polymul_status launch_ptrans(const PtParams& P, hipStream_t s) {
-  if (allow_lds<k_ptrans<L, LK>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
+template <typename W, int L, int LK>
+polymul_status launch_ptrans(const PtParams<W>& P, hipStream_t s) {
+  if (allow_lds<k_ptrans<W, L, LK>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
   constexpr uint32_t G = 16 >> LK;
   const uint64_t groups = (P.nprod + G - 1) / G;
   if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
-  hipLaunchKernelGGL((ptrans_kernel<L, LK>), dim3((uint32_t)groups), dim3(kThreads), pt_lds_bytes<L>(), s, P);
+  hipLaunchKernelGGL((ptrans_kernel<W, L, LK>), dim3((uint32_t)groups), dim3(kThreads), (pt_lds_bytes<W, L>()), s, P);
   return launch_status();
 }
-template <int L>
-polymul_status launch_ptrans_L(const PtParams& P, hipStream_t s) {
+template <typename W, int L>
+polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
   switch (P.n) {
-    case 1024: return launch_ptrans<L, 2>(P, s);
-    case 2048: return launch_ptrans<L, 3>(P, s);
-    default: return launch_ptrans<L, 4>(P, s);
+    case 1024: return launch_ptrans<W, L, 2>(P, s);
+    case 2048: return launch_ptrans<W, L, 3>(P, s);
+    default: return launch_ptrans<W, L, 4>(P, s);
   }
 }
 
+// 32-bit words: n = 1024 .. 4096 unless a tile side was asked for.
 bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L) {
   if (n < 1024 || n > 4096) return false;
-  if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;  // a tile side was asked for
+  if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;
   for (uint32_t i = 0; i < lc; ++i)
     if (!ptrans_modulus(qs[i])) return false;
   return true;
@@ -622,19 +658,106 @@ bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L) {
 
 polymul_status run_ptrans(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
                           uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, hipStream_t s,
-                          uint32_t lrep, bool b_shared) {
-  PtParams P{};
+                          uint32_t lrep, bool b_shared, uint32_t outer_points = 1) {
+  PtParams<uint32_t> P{};
   P.a = a; P.b = b; P.c = c;
   P.nprod = nprod;
   P.n = n;
   P.lc = lc; P.nq_total = nq_total; P.l0 = l0; P.lrep = lrep;
   P.b_shared = b_shared ? 1u : 0u;
-  for (uint32_t i = 0; i < lc; ++i) fill_ptmod(P.mods[i], qs[i], L, 2 * n / kPtM);
+  for (uint32_t i = 0; i < lc; ++i) fill_ptmod(P.mods[i], qs[i], L, 2 * n / kPtM * outer_points);
   switch (L) {
-    case 2: return launch_ptrans_L<2>(P, s);
-    case 3: return launch_ptrans_L<3>(P, s);
-    default: return launch_ptrans_L<4>(P, s);
+    case 2: return launch_ptrans_L<uint32_t, 2>(P, s);
+    case 3: return launch_ptrans_L<uint32_t, 3>(P, s);
+    default: return launch_ptrans_L<uint32_t, 4>(P, s);
   }
+}
+
+// 64-bit words, one modulus: parameters for degree n = 1024 .. 4096, or false where the
+// transform does not take the modulus.  Limb counts 4, 6 and 8 have kernels.
+bool fill_ptrans64(PtParams<uint64_t>& P, const uint64_t* a, const uint64_t* b, uint64_t* c, uint32_t n, uint64_t q,
+                   uint64_t nprod, bool b_shared, uint32_t outer_points, int* L) {
+  if (!(q & 1) || q < 3) return false;
+  const int need = limbs_for_q64(q);
+  *L = need <= 4 ? 4 : need <= 6 ? 6 : 8;
+  P = PtParams<uint64_t>{};
+  P.a = a; P.b = b; P.c = c;
+  P.nprod = nprod;
+  P.n = n;
+  P.lc = 1; P.nq_total = 1; P.l0 = 0; P.lrep = 1;
+  P.b_shared = b_shared ? 1u : 0u;
+  return fill_ptmod(P.mods[0], q, *L, 2 * n / kPtM * outer_points);
+}
+polymul_status launch_ptrans64(const PtParams<uint64_t>& P, int L, hipStream_t s) {
+  switch (L) {
+    case 4: return launch_ptrans_L<uint64_t, 4>(P, s);
+    case 6: return launch_ptrans_L<uint64_t, 6>(P, s);
+    default: return launch_ptrans_L<uint64_t, 8>(P, s);
+  }
+}
+
+// Degrees 8192 .. 65536 through an outer transform: 2k points of degree 4096 per operand in
+// the workspace, 4 n words per product, the points' products over a's points.
+template <typename W, int LK>
+polymul_status launch_outer(const PtOuter<W>& P, uint64_t products, bool inverse, hipStream_t s) {
+  const dim3 grid((uint32_t)(products * 16), inverse ? 1 : 2);
+  if (inverse) hipLaunchKernelGGL((pt_outer_inverse_kernel<W, LK>), grid, dim3(256), 0, s, P);
+  else hipLaunchKernelGGL((pt_outer_forward_kernel<W, LK>), grid, dim3(256), 0, s, P);
+  return launch_status();
+}
+template <typename W>
+polymul_status launch_outer_n(const PtOuter<W>& P, uint64_t n, uint64_t products, bool inverse, hipStream_t s) {
+  if (products * 16 > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
+  switch (n) {
+    case 8192: return launch_outer<W, 1>(P, products, inverse, s);
+    case 16384: return launch_outer<W, 2>(P, products, inverse, s);
+    case 32768: return launch_outer<W, 3>(P, products, inverse, s);
+    default: return launch_outer<W, 4>(P, products, inverse, s);
+  }
+}
+
+template <typename W>
+void fill_outer(PtOuter<W>& O, const W* a, const W* b, W* c, uint64_t n, uint64_t products, uint32_t L, void* ws) {
+  O = PtOuter<W>{};
+  O.a = a; O.b = b; O.c = c;
+  O.sa = (W*)ws;
+  O.sb = O.sa + 2 * n * products;
+  O.L = L;
+}
+
+// RNS products of degree n >= 8192 whose moduli ptrans_modulus takes; L <= kMaxQ.
+polymul_status run_outer32(const uint32_t* a, const uint32_t* b, uint32_t* c, uint64_t n, const uint32_t* q, uint32_t L,
+                           uint64_t batch, void* ws, hipStream_t s) {
+  const uint64_t products = batch * L;
+  const uint32_t points = (uint32_t)(2 * n / kPtOuterM);
+  const int Lq = limbs32(q, L);
+  PtOuter<uint32_t> O;
+  fill_outer(O, a, b, c, n, products, L, ws);
+  for (uint32_t l = 0; l < L; ++l) O.mods[l] = make_mod32(q[l], Lq);
+  polymul_status st = launch_outer_n(O, n, products, false, s);
+  if (st == POLYMUL_OK)
+    st = run_ptrans(O.sa, O.sb, O.sa, kPtOuterM, q, L, L, 0, products * points, Lq, s, points, false, points);
+  return st == POLYMUL_OK ? launch_outer_n(O, n, products, true, s) : st;
+}
+polymul_status run_outer64(const uint64_t* a, const uint64_t* b, uint64_t* c, uint64_t n, uint64_t batch,
+                           const PtParams<uint64_t>& inner, int Lq, void* ws, hipStream_t s) {
+  PtOuter<uint64_t> O;
+  fill_outer(O, a, b, c, n, batch, 1, ws);
+  O.mods[0] = inner.mods[0].m;
+  PtParams<uint64_t> P = inner;
+  P.a = O.sa; P.b = O.sb; P.c = O.sa;
+  polymul_status st = launch_outer_n(O, n, batch, false, s);
+  if (st == POLYMUL_OK) st = launch_ptrans64(P, Lq, s);
+  return st == POLYMUL_OK ? launch_outer_n(O, n, batch, true, s) : st;
+}
+
+// Negacyclic 64-bit products (one modulus) without a workspace.
+polymul_status run_u64(const uint64_t* a, const uint64_t* b, uint64_t* c, uint32_t n, uint64_t q, uint64_t batch,
+                       hipStream_t s, bool b_shared) {
+  PtParams<uint64_t> P;
+  int L;
+  if (n >= 1024 && n <= 4096 && fill_ptrans64(P, a, b, c, n, q, batch, b_shared, 1, &L)) return launch_ptrans64(P, L, s);
+  return run_stream<uint64_t>(a, b, c, n, &q, 1, 1, 0, batch, s, false, 1, b_shared);
 }
 
 // nprod products (i -> global (i/lc)*nq_total + l0 + i%lc) with moduli qs[0..lc <= kMaxQ).
@@ -730,9 +853,22 @@ polymul_status kara_workspace(uint64_t n, uint64_t products, uint32_t depth, uin
 }
 
 // The RNS Karatsuba route on validated arguments with a workspace of at least
-// kara_workspace(n, batch * L, depth, 4) bytes: split, sub-products, combine.
+// kara_workspace(n, batch * L, depth, 4) bytes: split, sub-products, combine.  choose: the
+// depth is the library's to pick and nothing was tuned, so the transform goes first (its 4 n
+// words per product are within the 6.75 n of the two levels built in from n = 1024 on).
 polymul_status run_rns_karatsuba(const uint32_t* a, const uint32_t* b, uint32_t* c, uint64_t n, const uint32_t* q,
-                                 uint32_t L, uint64_t batch, uint32_t depth, void* workspace, hipStream_t stream) {
+                                 uint32_t L, uint64_t batch, uint32_t depth, bool choose, void* workspace,
+                                 hipStream_t stream) {
+  if (choose && n >= 1024) {
+    bool odd = true;
+    for (uint32_t l = 0; l < L; ++l) odd = odd && ptrans_modulus(q[l]);
+    const int Lq = limbs32(q, L);
+    // at n = 8192 two Karatsuba levels (nine sub-products of degree 2048 on the transform) are
+    // ahead: 128 against 165 us for 512 products
+    if (odd && n > 8192) return run_outer32(a, b, c, n, q, L, batch, workspace, stream);
+    if (odd && n <= 4096 && ptrans_takes((uint32_t)n, q, L, Lq))
+      return run_ptrans(a, b, c, (uint32_t)n, q, L, L, 0, batch * L, Lq, stream, 1, false);
+  }
   const uint32_t nsub = depth == 1 ? 3 : depth == 2 ? 9 : 27;
   const uint32_t np = (uint32_t)(n >> depth);
   const uint64_t nprod = batch * L;
@@ -1026,7 +1162,7 @@ polymul_status polymul_negacyclic_u64(const uint64_t* a, const uint64_t* b, uint
   uint64_t bytes;
   polymul_status st = check_arrays(a, b, c, n, batch, 1, 8, &bytes);
   if (st != POLYMUL_OK || batch == 0) return st;
-  return run_stream<uint64_t>(a, b, c, (uint32_t)n, &q, 1, 1, 0, batch, stream);
+  return run_u64(a, b, c, (uint32_t)n, q, batch, stream, false);
 }
 
 polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* groups, uint32_t ngroups,
@@ -1310,7 +1446,7 @@ polymul_status polymul_negacyclic_u64_shared(const uint64_t* a, const uint64_t* 
   if (q < 2) return POLYMUL_EINVAL;
   polymul_status st = check_shared(a, b, c, n, batch, 1, 8);
   if (st != POLYMUL_OK || batch == 0) return st;
-  return run_stream<uint64_t>(a, b, c, (uint32_t)n, &q, 1, 1, 0, batch, stream, false, 1, true);
+  return run_u64(a, b, c, (uint32_t)n, q, batch, stream, true);
 }
 
 polymul_status polymul_karatsuba_workspace_size(uint64_t n, uint32_t L, uint64_t batch, uint32_t depth,
@@ -1327,6 +1463,7 @@ polymul_status polymul_negacyclic_u64_karatsuba(const uint64_t* a, const uint64_
                                                 uint64_t q, uint64_t batch, uint32_t depth, void* workspace,
                                                 uint64_t workspace_bytes, hipStream_t stream) {
   if (q < 2 || !is_pow2(n) || n > 65536) return POLYMUL_EINVAL;
+  const bool choose = depth == 0 && kara_tuned(n, batch, true) == kNotTuned;
   if (depth == 0) {
     depth = kara_depth_for(n, batch, true);
     if (depth == 0) return polymul_negacyclic_u64(a, b, c, n, q, batch, stream);
@@ -1340,6 +1477,13 @@ polymul_status polymul_negacyclic_u64_karatsuba(const uint64_t* a, const uint64_
   if (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need) return POLYMUL_EINVAL;
   if (overlaps(workspace, need, a, bytes) || overlaps(workspace, need, b, bytes) || overlaps(workspace, need, c, bytes))
     return POLYMUL_EALIAS;
+  if (choose && n >= 1024) {  // the transform, where it takes the modulus
+    const uint32_t points = n > kPtOuterM ? (uint32_t)(2 * n / kPtOuterM) : 1;
+    PtParams<uint64_t> P;
+    int Lq;
+    if (fill_ptrans64(P, a, b, c, (uint32_t)std::min<uint64_t>(n, kPtOuterM), q, batch * points, false, points, &Lq))
+      return points > 1 ? run_outer64(a, b, c, n, batch, P, Lq, workspace, stream) : launch_ptrans64(P, Lq, stream);
+  }
   const uint32_t nsub = depth == 1 ? 3 : depth == 2 ? 9 : 27;
   const uint32_t np = (uint32_t)(n >> depth);
   const uint64_t sub_words = batch * nsub * np;
@@ -1392,6 +1536,7 @@ polymul_status polymul_negacyclic_rns_karatsuba(const uint32_t* a, const uint32_
                                                 const uint32_t* q, uint32_t L, uint64_t batch, uint32_t depth,
                                                 void* workspace, uint64_t workspace_bytes, hipStream_t stream) {
   if (!is_pow2(n) || n > 65536 || L == 0 || L > 16) return POLYMUL_EINVAL;
+  const bool choose = depth == 0 && kara_tuned(n, batch * L, false) == kNotTuned;
   if (depth == 0) {
     depth = kara_depth_for(n, batch * L, false);
     if (depth == 0) return polymul_negacyclic_rns(a, b, c, n, q, L, batch, stream);
@@ -1402,13 +1547,14 @@ polymul_status polymul_negacyclic_rns_karatsuba(const uint32_t* a, const uint32_
   if (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need) return POLYMUL_EINVAL;
   if (overlaps(workspace, need, a, bytes) || overlaps(workspace, need, b, bytes) || overlaps(workspace, need, c, bytes))
     return POLYMUL_EALIAS;
-  return run_rns_karatsuba(a, b, c, n, q, L, batch, depth, workspace, stream);
+  return run_rns_karatsuba(a, b, c, n, q, L, batch, depth, choose, workspace, stream);
 }
 
 polymul_status polymul_negacyclic_rns_karatsuba_noalloc(const uint32_t* a, const uint32_t* b, uint32_t* c,
                                                         uint64_t n, const uint32_t* q, uint32_t L, uint64_t batch,
                                                         uint32_t depth, hipStream_t stream) {
   if (!is_pow2(n) || n > 65536 || L == 0 || L > 16) return POLYMUL_EINVAL;
+  const bool choose = depth == 0 && kara_tuned(n, batch * L, false) == kNotTuned;
   if (depth == 0) {
     depth = kara_depth_for(n, batch * L, false);
     if (depth == 0) return polymul_negacyclic_rns(a, b, c, n, q, L, batch, stream);
@@ -1425,7 +1571,7 @@ polymul_status polymul_negacyclic_rns_karatsuba_noalloc(const uint32_t* a, const
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st != POLYMUL_OK) return st;
-  return run_rns_karatsuba(a, b, c, n, q, L, batch, depth, ws, stream);
+  return run_rns_karatsuba(a, b, c, n, q, L, batch, depth, choose, ws, stream);
 }
 
 polymul_status polymul_tune_set(uint64_t n, uint32_t L, uint32_t t) {

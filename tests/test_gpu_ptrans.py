@@ -70,3 +70,53 @@ def test_a_tile_side_turns_the_route_off_with_the_same_result():
     finally:
         pm.polymul_tune_set(2048, 4, 0)
     check(want, oracle.negacyclic(a, b, Q30), "transform")
+
+
+GOLDILOCKS = (1 << 64) - (1 << 32) + 1
+
+
+def edge_operands64(rng, batch, n, q):
+    a = rng.integers(0, q, size=(batch, n), dtype=np.uint64)
+    b = rng.integers(0, q, size=(batch, n), dtype=np.uint64)
+    if batch > 3:
+        a[0], b[0] = q - 1, q - 1
+        a[1] = 0
+        if q >= 1 << 32:  # the oracle reads operands of smaller moduli as 32-bit words
+            a[2] = rng.integers(0, 1 << 64, size=n, dtype=np.uint64)
+            b[2] = rng.integers(0, 1 << 64, size=n, dtype=np.uint64)
+        a[3], b[3] = np.uint64(q - 1) * (np.arange(n, dtype=np.uint64) % 2), q // 2
+    return a, b
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096])
+@pytest.mark.parametrize("q", [3, 65537, (1 << 32) - 5, (1 << 36) - 5, (1 << 48) - 59, (1 << 48) + 21, (1 << 63) - 25,
+                               (1 << 63) + 29, 0x7F7F7F7F7F7F7F7F, 0x7F7F7F7F7F7F7F81, GOLDILOCKS, (1 << 64) - 1,
+                               (1 << 54) - 32])
+def test_moduli64(n, q):
+    rng = np.random.default_rng([n, q & 0xFFFFFFFF, q >> 32])
+    a, b = edge_operands64(rng, 5, n, q)
+    da, db = to_dev(a), to_dev(b)
+    want = oracle.negacyclic(a, b, q)
+    check(to_host(pm.polymul_negacyclic_u64(da, db, q), np.uint64), want, f"n={n}, q={q}")
+    shared = oracle.negacyclic(a, np.ascontiguousarray(np.broadcast_to(b[4], b.shape)), q)
+    check(to_host(pm.polymul_negacyclic_u64_shared(da, db[4].clone(), q), np.uint64), shared, f"shared n={n}, q={q}")
+    check(to_host(pm.polymul_negacyclic_u64_karatsuba(da, db, q, 0), np.uint64), want, f"depth 0 n={n}, q={q}")
+
+
+@pytest.mark.parametrize("n,batch", [(8192, 5), (16384, 4), (32768, 1), (65536, 1)])
+def test_outer_transform(n, batch):
+    """Degrees above 4096: the route with a workspace, and the direct calls that take one from torch."""
+    rng = np.random.default_rng(n)
+    for q in (GOLDILOCKS, (1 << 36) - 5):
+        a, b = edge_operands64(rng, batch, n, q)
+        want = oracle.negacyclic(a, b, q)
+        check(to_host(pm.polymul_negacyclic_u64_karatsuba(to_dev(a), to_dev(b), q, 0), np.uint64), want, f"{n}, {q}")
+        check(to_host(pm.polymul_negacyclic_u64(to_dev(a), to_dev(b), q), np.uint64), want, f"direct {n}, {q}")
+    qs = [Q30, Q_TOP, 3329]
+    pairs = [edge_operands(rng, batch, n, q) for q in qs]
+    a, b = (np.ascontiguousarray(np.stack([p[i] for p in pairs], axis=1)) for i in (0, 1))
+    want = oracle.negacyclic_rns(a, b, qs)
+    check(to_host(pm.polymul_negacyclic_rns_karatsuba(to_dev(a), to_dev(b), qs, 0), np.uint32), want, f"rns {n}")
+    check(to_host(pm.polymul_negacyclic_rns(to_dev(a), to_dev(b), qs), np.uint32), want, f"rns direct {n}")
+    check(to_host(pm.polymul_negacyclic(to_dev(a[:, 0].copy()), to_dev(b[:, 0].copy()), Q30), np.uint32),
+          np.ascontiguousarray(want[:, 0]), f"direct {n}")
