@@ -168,10 +168,61 @@ def _rns_shape(a, b, qs):
     return batch, L, n
 
 
+# Products of degree _WS_DEGREE and above run fastest through a workspace (an outer
+# polynomial transform around the one of degree 4096; odd moduli).  The direct calls take it
+# from torch's caching allocator, about _WS_BYTES at a time, and go without where that would
+# not be safe or there is no room.
+_WS_DEGREE = 8192
+_WS_BYTES = 512 << 20
+_WS_MAX_Q32 = 0x7F7F7F7F
+
+
+def _large(n, rows):
+    return rows > 0 and _WS_DEGREE <= n <= 65536 and n & (n - 1) == 0
+
+
+def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
+    """call(a, b, c pointers, rows, workspace pointer, its bytes, stream) over the `rows` rows of
+    a, b and c, in chunks with a workspace of size(rows of the chunk) bytes; False where nothing
+    was launched.  The workspace is torch memory of the current stream, so only calls on that
+    stream, on the tensors' own device, take it."""
+    import torch
+    if not a.is_cuda or a.device.index != torch.cuda.current_device():
+        return False
+    raw = _stream(stream)
+    if stream is not None and raw.value != _stream(None).value:
+        return False
+    chunk = max(1, min(rows, _WS_BYTES * rows // max(1, size(rows))))
+    need = max(16, size(chunk), size(rows % chunk) if rows % chunk else 0)
+    try:
+        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+    except torch.cuda.OutOfMemoryError:
+        return False
+    pa, pb, pc = _words(a, nbytes, "a").value, _words(b, nbytes, "b").value, _words(c, nbytes, "out").value
+    step = a.numel() // rows * nbytes
+    for r in range(0, rows, chunk):
+        _check(call(pa + r * step, pb + r * step, pc + r * step, min(chunk, rows - r), ws.data_ptr(), need, raw), name)
+    return True
+
+
+def _rns_through_workspace(name, a, b, c, n, qs, batch, stream):
+    L = len(qs)
+    if L > 16 or not _large(n, batch) or not all(q & 1 and q <= _WS_MAX_Q32 for q in qs):
+        return False
+    lib = load_library()
+    qarr = (ctypes.c_uint32 * L)(*qs)
+    return _through_workspace(
+        name, 4, a, b, c, n, batch, stream, lambda rows: polymul_karatsuba_workspace_size(n, L, rows, 0),
+        lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_rns_karatsuba(
+            pa, pb, pc, n, ctypes.cast(qarr, ctypes.c_void_p), L, rows, 0, ws, size, st))
+
+
 def polymul_negacyclic(a, b, q, out=None, stream=None):
     """c = a*b in Z_q[x]/(x^n+1) for 32-bit words [..., n], q < 2^32 (int8-MFMA path)."""
     n, batch = _pair(a, b)
     c = _result(out, a, 4)
+    if n >= _WS_DEGREE and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
+        return c
     st = load_library().polymul_negacyclic(_words(a, 4, "a"), _words(b, 4, "b"), _words(c, 4, "out"),
                                           n, int(q), batch, _stream(stream))
     _check(st, "polymul_negacyclic")
@@ -192,6 +243,14 @@ def polymul_negacyclic_u64(a, b, q, out=None, stream=None):
     """c = a*b in Z_q[x]/(x^n+1) for 64-bit words [..., n], q < 2^64."""
     n, batch = _pair(a, b)
     c = _result(out, a, 8)
+    if _large(n, batch) and int(q) & 1:
+        lib = load_library()
+        if _through_workspace(
+                "polymul_negacyclic_u64", 8, a, b, c, n, batch, stream,
+                lambda rows: polymul_karatsuba_u64_workspace_size(n, rows, 0),
+                lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_u64_karatsuba(
+                    pa, pb, pc, n, int(q), rows, 0, ws, size, st)):
+            return c
     st = load_library().polymul_negacyclic_u64(_words(a, 8, "a"), _words(b, 8, "b"), _words(c, 8, "out"),
                                               n, int(q), batch, _stream(stream))
     _check(st, "polymul_negacyclic_u64")
@@ -221,6 +280,9 @@ def polymul_negacyclic_rns(a, b, qs, out=None, stream=None):
     """RNS form: a, b are 32-bit words [batch, L, n]; channel l is taken mod qs[l]."""
     batch, L, n = _rns_shape(a, b, qs)
     c = _result(out, a, 4)
+    if n >= _WS_DEGREE and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
+                                                  stream):
+        return c
     qarr = (ctypes.c_uint32 * L)(*[int(x) for x in qs])
     st = load_library().polymul_negacyclic_rns(_words(a, 4, "a"), _words(b, 4, "b"), _words(c, 4, "out"),
                                               n, ctypes.cast(qarr, ctypes.c_void_p), L, batch, _stream(stream))

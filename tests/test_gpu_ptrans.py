@@ -120,3 +120,24 @@ def test_outer_transform(n, batch):
     check(to_host(pm.polymul_negacyclic_rns(to_dev(a), to_dev(b), qs), np.uint32), want, f"rns direct {n}")
     check(to_host(pm.polymul_negacyclic(to_dev(a[:, 0].copy()), to_dev(b[:, 0].copy()), Q30), np.uint32),
           np.ascontiguousarray(want[:, 0]), f"direct {n}")
+
+
+def test_direct_call_in_chunks_and_on_another_stream(monkeypatch):
+    rng = np.random.default_rng(8)
+    a, b = edge_operands64(rng, 5, 8192, GOLDILOCKS)
+    want = oracle.negacyclic(a, b, GOLDILOCKS)
+    da, db = to_dev(a), to_dev(b)
+    import torch
+    from paper_2307_06554_amd import binding
+    per_row = pm.polymul_karatsuba_u64_workspace_size(8192, 1, 0)
+    monkeypatch.setattr(binding, "_WS_BYTES", 2 * per_row)  # chunks of 2, 2 and 1 products
+    check(to_host(pm.polymul_negacyclic_u64(da, db, GOLDILOCKS), np.uint64), want, "chunks")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    c = torch.full_like(da, -1)
+    pm.polymul_negacyclic_u64(da, db, GOLDILOCKS, out=c, stream=s)  # not torch's current stream: no workspace
+    check(to_host(c, np.uint64), want, "stream argument")
+    with torch.cuda.stream(s):
+        got = pm.polymul_negacyclic_u64(da, db, GOLDILOCKS)
+    s.synchronize()
+    check(to_host(got, np.uint64), want, "current stream")
