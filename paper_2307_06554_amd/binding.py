@@ -168,17 +168,17 @@ def _rns_shape(a, b, qs):
     return batch, L, n
 
 
-# Products of degree _WS_DEGREE and above run fastest through a workspace (an outer
-# polynomial transform around the one of degree 4096; odd moduli).  The direct calls take it
+# Products of degree _WS_DEGREE[bytes per word] and above run fastest through a workspace (an
+# outer polynomial transform around the one of degree 4096; odd moduli).  The direct calls take it
 # from torch's caching allocator, about _WS_BYTES at a time, and go without where that would
 # not be safe or there is no room.
-_WS_DEGREE = 8192
+_WS_DEGREE = {4: 16384, 8: 8192}
 _WS_BYTES = 512 << 20
 _WS_MAX_Q32 = 0x7F7F7F7F
 
 
-def _large(n, rows):
-    return rows > 0 and _WS_DEGREE <= n <= 65536 and n & (n - 1) == 0
+def _large(n, rows, nbytes):
+    return rows > 0 and _WS_DEGREE[nbytes] <= n <= 65536 and n & (n - 1) == 0
 
 
 def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
@@ -207,7 +207,7 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
 
 def _rns_through_workspace(name, a, b, c, n, qs, batch, stream):
     L = len(qs)
-    if L > 16 or not _large(n, batch) or not all(q & 1 and q <= _WS_MAX_Q32 for q in qs):
+    if L > 16 or not _large(n, batch, 4) or not all(q & 1 and q <= _WS_MAX_Q32 for q in qs):
         return False
     lib = load_library()
     qarr = (ctypes.c_uint32 * L)(*qs)
@@ -221,7 +221,7 @@ def polymul_negacyclic(a, b, q, out=None, stream=None):
     """c = a*b in Z_q[x]/(x^n+1) for 32-bit words [..., n], q < 2^32 (int8-MFMA path)."""
     n, batch = _pair(a, b)
     c = _result(out, a, 4)
-    if n >= _WS_DEGREE and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
+    if n >= _WS_DEGREE[4] and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
         return c
     st = load_library().polymul_negacyclic(_words(a, 4, "a"), _words(b, 4, "b"), _words(c, 4, "out"),
                                           n, int(q), batch, _stream(stream))
@@ -243,7 +243,7 @@ def polymul_negacyclic_u64(a, b, q, out=None, stream=None):
     """c = a*b in Z_q[x]/(x^n+1) for 64-bit words [..., n], q < 2^64."""
     n, batch = _pair(a, b)
     c = _result(out, a, 8)
-    if _large(n, batch) and int(q) & 1:
+    if _large(n, batch, 8) and int(q) & 1:
         lib = load_library()
         if _through_workspace(
                 "polymul_negacyclic_u64", 8, a, b, c, n, batch, stream,
@@ -280,7 +280,7 @@ def polymul_negacyclic_rns(a, b, qs, out=None, stream=None):
     """RNS form: a, b are 32-bit words [batch, L, n]; channel l is taken mod qs[l]."""
     batch, L, n = _rns_shape(a, b, qs)
     c = _result(out, a, 4)
-    if n >= _WS_DEGREE and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
+    if n >= _WS_DEGREE[4] and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
                                                   stream):
         return c
     qarr = (ctypes.c_uint32 * L)(*[int(x) for x in qs])

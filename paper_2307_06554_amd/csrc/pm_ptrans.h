@@ -1,61 +1,76 @@
-// Products of degree 1024..4096 through a polynomial transform (H. J. Nussbaumer, "Fast
+// Products of degree 1024..8192 through a polynomial transform (H. J. Nussbaumer, "Fast
 // polynomial transform algorithms for digital convolution", IEEE Trans. ASSP 28, 1980),
 // the matrix products of Eq. (3) running on its 2k pieces.
 //
-// Write n = k M with M = 256 and y = x^k.  A polynomial a = sum_{i<k} x^i A_i(y), A_i[j] =
-// a[i + k j], has its coefficients in R = Z_q[y]/(y^M + 1), where w = y^(M/k) is a 2k-th
-// root of one with w^k = -1: multiplying by a power of w is a signed rotation, no roots in
-// Z_q are needed and any odd q will do.  So
+// Write n = k M with M = 256 (512 at n = 8192) and y = x^k.  A polynomial a = sum_{i<k} x^i
+// A_i(y), A_i[j] = a[i + k j], has its coefficients in R = Z_q[y]/(y^M + 1), where w = y^(M/k)
+// is a 2k-th root of one with w^k = -1: multiplying by a power of w is a signed rotation, no
+// roots in Z_q are needed and any odd q will do.  So
 //   A^_s = sum_i w^(i s) A_i,   C^_s = A^_s B^_s in R,   P_i = (1/2k) sum_s w^(-i s) C^_s,
 //   c = sum_{i<k} x^i (P_i + y P_(i+k))                  (s < 2k; x^k = y folds the top half)
 // and one product of degree bound n is 2k negacyclic products of degree bound M: 2k M^2 =
-// 2 n M multiply-adds on the matrix units for n^2 (an eighth at n = 4096), and 3 log2(2k)
-// additions mod q per coefficient.  With P_i and P_(i+k) the sum and difference of the
-// even and odd points' halves, the fold is (1 + y) E_i + w^(-i) (1 - y) O_i: the factors
+// 2 n M multiply-adds on the matrix units for n^2 (an eighth at n = 4096 and 8192), and
+// 3 log2(2k) additions mod q per coefficient.  With P_i and P_(i+k) the sum and difference of
+// the even and odd points' halves, the fold is (1 + y) E_i + w^(-i) (1 - y) O_i: the factors
 // 1 +- y are applied to C^_s, where a neighbouring column is at hand.
 //
-// A workgroup (four waves) takes G = 16 / k products.  A thread owns one column j = ylow +
-// 16 yhigh of them, yhigh = lane % 16, ylow = 4 wave + lane / 16, and holds the 32 points
-// of both operands in registers: w^e moves yhigh only, so a rotation is a DPP row rotation
-// that the butterfly's addition takes as its operand, and the sign is a select on constant
-// lane masks.  The 32 sub-products then pass through LDS eight at a time: four points of
-// the four threads of a column group are transposed (v_permlane{32,16}_swap) so that each
-// thread packs four consecutive coefficients of one point, their digit planes (layout of
-// the 16x16-tile kernel: t = 16, r = 16, K = 256) are multiplied by v_mfma_i32_16x16x64_i8,
-// two sub-products per wave, and the results return to their columns as words.
+// A workgroup takes G = 16 / k products.  A thread holds 32 points of one column j = ylow +
+// (M / 16) yhigh, yhigh = lane % 16: w^e moves yhigh only, so a rotation is a DPP row rotation
+// that the butterfly's addition takes as its operand, and the sign is a select on constant lane
+// masks.  The 32 sub-products then pass through LDS eight at a time: four points of four
+// neighbouring columns are transposed (v_permlane{32,16}_swap) so that each thread packs four
+// consecutive coefficients of one point, their digit planes (layout of the 16x16-tile kernel:
+// t = 16, r = M / 16, K = M) are multiplied by v_mfma_i32_16x16x64_i8, and the results return to
+// their columns as words.
 //
 // Recombination of a sub-product is one Montgomery step: x = lift + sum_s T_s rc_s with
 // rc_s = 2^(8s) 2^32 / (2k) mod q, centred.  |T_s| <= P_s M 2^14 and sum_s P_s = L^2, so
-// |sum| <= lift = q L^2 M 2^13 <= q 2^25, x is below q 2^32 and hi(x) - hi(m q) lies in
+// |sum| <= lift = q L^2 M 2^13 <= q 2^26, x is below q 2^32 and hi(x) - hi(m q) lies in
 // (-q, q).
 //
-// Measured against the 32x32-tile kernel on whole products, us per call: n = 4096, 2048
-// products 364 -> 92 and 8 products 38.8 -> 18.0; n = 1024, 4095 products 55.5 -> 42.4
-// (30-bit moduli).  That kernel was bound by the power its matrix units draw; here they do
-// an eighth (n = 4096) or half (n = 1024) of the work and the vector units' additions,
-// digit splits and recombinations weigh as much.
+// Measured against the 32x32-tile kernel on whole products, us per call (30-bit moduli):
+// n = 4096, 2048 products 364 -> 82 and 8 products 38.8 -> 14.2; n = 1024, 4095 products 55.5
+// -> 41.5; n = 8192, 512 products, 244 through two Karatsuba levels -> 77.  That kernel was bound
+// by the power its matrix units draw.  Here the K loops take half of the time (left out, the
+// n = 4096 batch takes 42 us of 82): a step of sixteen MFMAs (256 cycles on each SIMD) reads
+// 9 KiB, the A runs five dwords a lane at 128 B a cycle, so four SIMDs' steps keep the LDS busy
+// for nearly as long as the matrix units; the rest is the vector units' additions, digit splits
+// and recombinations, which overlap with the other waves' products.
 //
 // 64-bit words (one modulus, 4, 6 or 8 limbs): the same with 64-bit additions and a 64-bit
-// Montgomery step, two waves per SIMD.  Sixteen products of n = 65536 with q = 2^64 - 2^32
-// + 1, through the outer transform below: 3.03 ms on the streaming kernel, 1.41 ms through
-// three Karatsuba levels, 113 us here.
+// Montgomery step.  Sixteen products of n = 65536 with q = 2^64 - 2^32 + 1, through the outer
+// transform below: 3.03 ms on the streaming kernel, 1.41 ms through three Karatsuba levels,
+// 115 us here.
 #pragma once
 #include "pm_mfma16.h"
 #include "pm_stream.h"
 
 namespace pm {
 
-constexpr int kPtM = 256;             // degree bound of the sub-products
 constexpr int kPtPoints = 32;         // sub-products per workgroup
 constexpr int kPtBatch = 8;           // of them in LDS at a time
-constexpr uint32_t kPtAPlane = 272;   // reversed ext positions 0 .. 271: 255 .. -16
-constexpr uint32_t kPtBPlane = 31 * 16;  // rows -15 .. 15
-constexpr uint32_t kPtRow = 80;       // words between the four result rows of a sub-product
-constexpr uint32_t kPtSubWords = 4 * kPtRow;
-template <int L>
-constexpr uint32_t pt_sub_bytes() { return (uint32_t)L * (kPtAPlane + kPtBPlane); }
-template <typename W, int L>
-constexpr uint32_t pt_lds_bytes() { return kPtBatch * (pt_sub_bytes<L>() + kPtSubWords * (uint32_t)sizeof(W)); }
+constexpr uint32_t kPtRow = 80;       // words between the four result rows of a column group
+
+// Sub-products of degree bound M = 256 C: a thread owns C columns.
+template <int C>
+struct PtGeom {
+  static constexpr int kM = 256 * C, kR = 16 * C;             // M = 16 R
+  static constexpr uint32_t kAPlane = kM + 16;                // reversed ext positions: M - 1 .. -16
+  static constexpr uint32_t kBPlane = (2 * kR - 1) * 16;      // rows -(R - 1) .. R - 1
+  static constexpr uint32_t kColWords = 4 * kPtRow + (C > 1 ? 16 : 0);  // results of the c-th columns
+  static constexpr uint32_t kResWords = C * kColWords;
+  template <int L> static constexpr uint32_t sub_bytes() { return (uint32_t)L * (kAPlane + kBPlane); }
+};
+// LDS: the planes of a batch (in the end the words two halves swap), then its results.
+template <typename W, int L, int C, int H>
+constexpr uint32_t pt_results_at() {
+  const uint32_t planes = kPtBatch * PtGeom<C>::template sub_bytes<L>(), swap = H == 1 ? 0 : 16 * 256 * C * (uint32_t)sizeof(W);
+  return planes > swap ? planes : swap;
+}
+template <typename W, int L, int C, int H>
+constexpr uint32_t pt_lds_bytes() {
+  return pt_results_at<W, L, C, H>() + kPtBatch * PtGeom<C>::kResWords * (uint32_t)sizeof(W);
+}
 
 struct PtMod32 {
   ModQ32 m;
@@ -211,12 +226,20 @@ __device__ __forceinline__ void pt_forward(W* x, W* v, const M& m, uint32_t yhig
   pt_stages<4, 1, 2 * K>(v, (W)m.q, yhigh);
 }
 
-// c_i = +-(E_i + w^(-i) O_i) from the transformed even and odd points, in [0, q).
+// O_i <- w^(-i) O_i.
 template <int LK, int I, typename W>
-__device__ __forceinline__ void pt_last(const W* e, const W* o, W* c, W q, uint32_t yhigh) {
+__device__ __forceinline__ void pt_twist(W* o, W q, uint32_t yhigh) {
   if constexpr (I < (1 << LK)) {
-    c[I] = pt_close<(__builtin_popcount(I) & 1) != 0>(pt_shift<-I * (16 >> LK)>(o[I], q, yhigh), e[I], q);
-    pt_last<LK, I + 1>(e, o, c, q, yhigh);
+    o[I] = pt_shift<-I * (16 >> LK)>(o[I], q, yhigh);
+    pt_twist<LK, I + 1>(o, q, yhigh);
+  }
+}
+// c_i = +-(E_i + w^(-i) O_i), i in [I, END), in [0, q); e, t and c start at i = I.
+template <int I, int END, typename W>
+__device__ __forceinline__ void pt_last(const W* e, const W* t, W* c, W q) {
+  if constexpr (I < END) {
+    c[0] = pt_close<(__builtin_popcount(I) & 1) != 0>(t[0], e[0], q);
+    pt_last<I + 1, END>(e + 1, t + 1, c + 1, q);
   }
 }
 
@@ -243,7 +266,7 @@ __device__ __forceinline__ void pt_transpose(uint64_t (&w)[4]) {
 // Digit words of x in [0, q] and of -x, and their byte planes.
 template <int L>
 __device__ __forceinline__ void pt_digits(const uint32_t (&x)[4], const ModQ32& m, uint32_t (&pos)[4], uint32_t (&neg)[4]) {
-  digits_pm32<L>(x, m.q, m.thr, pos, neg);
+  digits_pm32<L>(x, m.q, L == 4 ? 0xFFFFFFFFu : m.thr, pos, neg);  // four limbs: q is within the window
 }
 template <int L>
 __device__ __forceinline__ void pt_digits(const uint64_t (&x)[4], const ModQ64& m, uint64_t (&pos)[4], uint64_t (&neg)[4]) {
@@ -263,40 +286,41 @@ __device__ __forceinline__ void pt_store(uint8_t* base, uint32_t plane, uint32_t
 }
 
 // Four points of the column group's four columns into the digit planes of sub-product
-// `sub` (this row's): the reversed ext of a, or the rows of b.
-template <int L, bool IS_B, typename W, typename M>
-__device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const M& m, uint32_t wave, uint32_t yhigh) {
+// `sub` (this row's): the reversed ext of a, or the rows of b.  brow: the columns' index / 16.
+template <int L, int C, bool IS_B, typename W, typename M>
+__device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const M& m, uint32_t wave, uint32_t brow) {
+  typedef PtGeom<C> G;
   W w[4] = {v[0], v[1], v[2], v[3]};
   pt_transpose(w);
   W pos[4], neg[4];
   if constexpr (IS_B) {
     pt_digits<L>(w, m, pos, neg);
-    uint8_t* rows = sub + L * kPtAPlane + 4 * wave;
-    pt_store<L>(rows, kPtBPlane, (yhigh + 15) * 16, pos);
-    if (yhigh > 0) pt_store<L>(rows, kPtBPlane, (yhigh - 1) * 16, neg);
+    uint8_t* rows = sub + L * G::kAPlane + 4 * wave;
+    pt_store<L>(rows, G::kBPlane, (brow + G::kR - 1) * 16, pos);
+    if (brow > 0) pt_store<L>(rows, G::kBPlane, (brow - 1) * 16, neg);
   } else {
     const W rev[4] = {w[3], w[2], w[1], w[0]};
     pt_digits<L>(rev, m, pos, neg);
-    const uint32_t off = 252 - 4 * wave - 16 * yhigh;
-    pt_store<L>(sub, kPtAPlane, off, pos);
-    if (yhigh == 15) pt_store<L>(sub, kPtAPlane, off + 256, neg);
+    const uint32_t off = G::kM - 4 - 4 * wave - 16 * brow;
+    pt_store<L>(sub, G::kAPlane, off, pos);
+    if (brow == G::kR - 1) pt_store<L>(sub, G::kAPlane, off + G::kM, neg);
   }
 }
 
 // K-step of a sub-product with more than four limbs: the B rows of all limbs are held, the
 // A runs are taken limb by limb.
 template <int L>
-__device__ __forceinline__ void pt_step_wide(v4i_acc (&acc)[2 * L - 1], const uint8_t* aplane, int S,
-                                             const uint8_t* bplane, int boff) {
+__device__ __forceinline__ void pt_step_wide(v4i_acc (&acc)[2 * L - 1], const uint8_t* aplane, uint32_t a_plane, int S,
+                                             const uint8_t* bplane, uint32_t b_plane, int boff) {
   v4i b[L];
 #pragma unroll
-  for (int j = 0; j < L; ++j) b[j] = *(const v4i*)(bplane + j * kPtBPlane + boff);
+  for (int j = 0; j < L; ++j) b[j] = *(const v4i*)(bplane + j * b_plane + boff);
   const uint32_t sh = (uint32_t)(S & 3);
   uint32_t x[2][5];
   load_run(x[0], aplane, S);
 #pragma unroll
   for (int i = 0; i < L; ++i) {
-    if (i + 1 < L) load_run(x[(i + 1) & 1], aplane + (i + 1) * kPtAPlane, S);
+    if (i + 1 < L) load_run(x[(i + 1) & 1], aplane + (i + 1) * a_plane, S);
     const v4i a = align_run(x[i & 1], sh);
 #pragma unroll
     for (int j = 0; j < L; ++j) acc[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b[j], acc[i + j], 0, 0, 0);
@@ -328,27 +352,32 @@ __device__ __forceinline__ uint64_t pt_recombine(const v4i_acc (&acc)[2 * L - 1]
   return pt_sub((uint64_t)(x1 >> 32), mulhi64(lo * pm.qinv, pm.m.q), pm.m.q);
 }
 
-// One sub-product from its planes to its words: lane (u, g) leaves coefficients 16 u + 4 g + e
-// in row e of res.  -c[255] goes to slot 64 of row 3, where column 0 finds y c.
-template <int L, typename W, typename PM>
-__device__ __forceinline__ void pt_multiply(const uint8_t* sub, W* res, const PM& pm, uint32_t lane) {
+// One 16x16 output tile (columns 16 tile + u) of a sub-product from its planes to its words:
+// lane (u, g) leaves coefficients 16 (16 tile + u) + 4 g + e in row e of the results of columns
+// (16 tile + u) % C.  -c[M - 1] goes to slot 64 of the last columns' row 3, where column 0
+// finds y c.
+template <int L, int C, typename W, typename PM>
+__device__ __forceinline__ void pt_multiply(const uint8_t* sub, W* res, const PM& pm, uint32_t lane, uint32_t tile) {
+  typedef PtGeom<C> G;
   const int zl = (int)(lane & 15), g = (int)(lane >> 4);
-  const int S0 = 255 - 16 * g - zl;
-  const int B0 = (zl + 15 - g) * 16;
-  const uint8_t* bp = sub + L * kPtAPlane;
+  const int S0 = G::kM - 1 - 16 * g - zl;
+  const int B0 = (16 * (int)tile + zl + G::kR - 1 - g) * 16;
+  const uint8_t* bp = sub + L * G::kAPlane;
   v4i_acc acc[2 * L - 1];
 #pragma unroll
   for (int s = 0; s < 2 * L - 1; ++s) acc[s] = v4i_acc{0, 0, 0, 0};
 #pragma unroll
-  for (int st = 0; st < kPtM / 64; ++st) {
-    if constexpr (L <= 4) mfma16_step<L>(acc, sub, kPtAPlane, S0 - 64 * st, bp, kPtBPlane, B0 - 64 * st);
-    else pt_step_wide<L>(acc, sub, S0 - 64 * st, bp, B0 - 64 * st);
+  for (int st = 0; st < G::kM / 64; ++st) {
+    if constexpr (L <= 4) mfma16_step<L>(acc, sub, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
+    else pt_step_wide<L>(acc, sub, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
   }
+  const uint32_t u = 16 * tile + zl;
+  W* out = C == 1 ? res + lane : res + (u % C) * G::kColWords + 16 * g + u / C;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const W r = pt_recombine<L>(acc, e, pm);
-    res[e * kPtRow + lane] = r;
-    if (e == 3 && lane == 63) res[3 * kPtRow + 64] = (W)pm.m.q - r;
+    out[e * kPtRow] = r;
+    if (e == 3 && lane == 63 && tile == C - 1) res[(C - 1) * G::kColWords + 3 * kPtRow + 64] = (W)pm.m.q - r;
   }
 }
 
@@ -380,85 +409,137 @@ __device__ __forceinline__ void pt_put(W* p, const W* x) {
   }
 }
 
-template <typename W, int L, int LK>
+// One workgroup of 4 C H waves: G = 16 / K products of degree bound K 256 C.  Wave: half, c, w
+// (w the lowest two bits); a thread owns column 16 c + 4 w + row of the rows of 16 C.  H = 1: it
+// holds both operands' points.  H = 2: half 0 transforms a and, in the end, the even points,
+// half 1 b and the odd ones; the two swap half of what they have for the last step.
+template <typename W, int L, int LK, int C, int H>
 __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uint8_t* smem) {
-  constexpr int K = 1 << LK, G = 16 >> LK, PTS = 2 * K;
+  typedef PtGeom<C> Geo;
+  constexpr int K = 1 << LK, G = 16 >> LK, PTS = 2 * K, OPS = 3 - H;
+  constexpr uint32_t kSub = Geo::template sub_bytes<L>();
   const uint32_t lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
-  const uint32_t yhigh = lane & 15, row = lane >> 4, ylow = 4 * wave + row;
-  const uint32_t j = ylow + 16 * yhigh;
+  const uint32_t w = wave & 3, c = (wave >> 2) & (C - 1), half = wave / (4 * C);
+  const uint32_t yhigh = lane & 15, row = lane >> 4;
+  const uint32_t j = 16 * c + 4 * w + row + Geo::kR * yhigh;
 
-  uint64_t off[G], boff[G];
+  uint64_t off[G];
   uint32_t li[G];
-  W va[kPtPoints], vb[kPtPoints];
+  W v[OPS][kPtPoints];
   {
-    W xa[16], xb[16];
+    W x[OPS][16];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const uint64_t p = grp * G + g;
       const uint64_t gp = global_product(P, p < P.nprod ? p : P.nprod - 1, &li[g]);
       off[g] = wave_uniform(gp * P.n);
-      boff[g] = wave_uniform(b_product(P, gp, li[g]) * P.n);
+      const uint64_t boff = wave_uniform(b_product(P, gp, li[g]) * P.n);
       li[g] = wave_uniform(li[g]);
-      pt_load<K>(P.a + off[g] + (size_t)K * j, xa + g * K);
-      pt_load<K>(P.b + boff[g] + (size_t)K * j, xb + g * K);
+      if constexpr (H == 1) {
+        pt_load<K>(P.a + off[g] + (size_t)K * j, x[0] + g * K);
+        pt_load<K>(P.b + boff + (size_t)K * j, x[OPS - 1] + g * K);
+      } else {
+        pt_load<K>((half ? P.b + boff : P.a + off[g]) + (size_t)K * j, x[0] + g * K);
+      }
     }
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      pt_forward<LK>(xa + g * K, va + g * PTS, P.mods[li[g]].m, yhigh);
-      pt_forward<LK>(xb + g * K, vb + g * PTS, P.mods[li[g]].m, yhigh);
-    }
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int o = 0; o < OPS; ++o) pt_forward<LK>(x[o] + g * K, v[o] + g * PTS, P.mods[li[g]].m, yhigh);
   }
 
-  W* results = (W*)(smem + kPtBatch * pt_sub_bytes<L>());
-  // column j of a sub-product's results, and column j - 1 (times y: -c[255] at j = 0)
-  const uint32_t cur = row * kPtRow + 16 * wave + yhigh;
-  const uint32_t prev = row > 0 ? cur - kPtRow
-                        : wave > 0 ? 3 * kPtRow + 16 * (wave - 1) + yhigh
-                        : yhigh > 0 ? 3 * kPtRow + 48 + yhigh - 1 : 3 * kPtRow + 64;
-  W ch[kPtPoints];  // C^_s (1 +- y) at column j, the even points of a product first
+  W* results = (W*)(smem + pt_results_at<W, L, C, H>());
+  // this thread's column of a sub-product's results, and the column before it (times y:
+  // -c[M - 1] before column 0)
+  const uint32_t cur = c * Geo::kColWords + row * kPtRow + 16 * w + yhigh;
+  const uint32_t prev = row > 0  ? cur - kPtRow
+                        : w > 0  ? c * Geo::kColWords + 3 * kPtRow + 16 * (w - 1) + yhigh
+                        : c > 0  ? (c - 1) * Geo::kColWords + 3 * kPtRow + 48 + yhigh
+                                 : (C - 1) * Geo::kColWords + 3 * kPtRow + (yhigh > 0 ? 48 + yhigh - 1 : 64);
+  // C^_s (1 +- y): of a product's points, the even ones first (H = 2: those of this half)
+  W ch[kPtPoints / H];
 #pragma unroll
   for (int ph = 0; ph < kPtPoints / kPtBatch; ++ph) {
     const int g = ph * kPtBatch / PTS;  // the batch's product
     const auto& pm = P.mods[li[g]];
 #pragma unroll
     for (int h = 0; h < kPtBatch; h += 4) {
-      uint8_t* sub = smem + (h + row) * pt_sub_bytes<L>();
-      pt_stage_planes<L, false>(va + ph * kPtBatch + h, sub, pm.m, wave, yhigh);
-      pt_stage_planes<L, true>(vb + ph * kPtBatch + h, sub, pm.m, wave, yhigh);
+      uint8_t* sub = smem + (h + row) * kSub;
+      if (H == 1 || half == 0)
+        pt_stage_planes<L, C, false>(v[0] + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c);
+      if (H == 1 || half == 1)
+        pt_stage_planes<L, C, true>(v[OPS - 1] + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c);
     }
     __syncthreads();
+    constexpr uint32_t kUnits = 2 / H;  // (sub-product, tile) units per wave
 #pragma unroll 1
-    for (uint32_t s = 2 * wave; s < 2 * wave + 2; ++s)
-      pt_multiply<L>(smem + s * pt_sub_bytes<L>(), results + s * kPtSubWords, pm, lane);
+    for (uint32_t i = kUnits * wave; i < kUnits * (wave + 1); ++i)
+      pt_multiply<L, C>(smem + i / C * kSub, results + i / C * Geo::kResWords, pm, lane, i % C);
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < kPtBatch; ++s) {
-      const W x = results[s * kPtSubWords + cur], y = results[s * kPtSubWords + prev];
-      const int pt = (ph * kPtBatch + s) % PTS;
+    for (int s = 0; s < kPtBatch; s += H) {
+      const W* res = results + (s + (H == 1 ? 0 : half)) * Geo::kResWords;
+      const int pt = (ph * kPtBatch + s) % PTS;  // H = 2: the even one of the halves' two
+      const W x = res[cur], y = res[prev];
       // decimation in time wants the points of each half in bit-reversed order
-      const int to = g * PTS + (pt & 1) * K + pt_bitrev(pt >> 1, LK);
-      ch[to] = pt & 1 ? pt_sub(x, y, (W)pm.m.q) : pt_add(x, y, (W)pm.m.q);
+      const int to = (H == 1 ? g * PTS + (pt & 1) * K : g * K) + pt_bitrev(pt >> 1, LK);
+      const W q = (W)pm.m.q;
+      if constexpr (H == 1) ch[to] = pt & 1 ? pt_sub(x, y, q) : pt_add(x, y, q);
+      else ch[to] = pt_add(x, half ? q - y : y, q);
     }
   }
+  if constexpr (H == 1) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const W q = (W)P.mods[li[g]].m.q;
-    W* e = ch + g * PTS;
-    W c[K];
-    pt_stages<2, -1, K>(e, q, yhigh);
-    pt_stages<2, -1, K>(e + K, q, yhigh);
-    pt_last<LK, 0>(e, e + K, c, q, yhigh);
-    if (grp * G + g < P.nprod) pt_put<K>(P.c + off[g] + (size_t)K * j, c);
+    for (int g = 0; g < G; ++g) {
+      const W q = (W)P.mods[li[g]].m.q;
+      W* e = ch + g * PTS;
+      W o[K];
+      pt_stages<2, -1, K>(e, q, yhigh);
+      pt_stages<2, -1, K>(e + K, q, yhigh);
+      pt_twist<LK, 0>(e + K, q, yhigh);
+      pt_last<0, K>(e, e + K, o, q);
+      if (grp * G + g < P.nprod) pt_put<K>(P.c + off[g] + (size_t)K * j, o);
+    }
+  } else {
+    // half h keeps the words of i in [h K / 2, (h + 1) K / 2) and hands over the others,
+    // through the planes' memory (last read before the last barrier)
+    constexpr uint32_t kCols = 256 * C;
+    W* give = (W*)smem + half * 8 * kCols + (threadIdx.x & (kCols - 1));
+    const W* take = (const W*)smem + (half ^ 1) * 8 * kCols + (threadIdx.x & (kCols - 1));
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const W q = (W)P.mods[li[g]].m.q;
+      W* e = ch + g * K;
+      pt_stages<2, -1, K>(e, q, yhigh);
+      if (half) pt_twist<LK, 0>(e, q, yhigh);
+#pragma unroll
+      for (int i = 0; i < K / 2; ++i) give[(g * K / 2 + i) * kCols] = half ? e[i] : e[K / 2 + i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const W q = (W)P.mods[li[g]].m.q;
+      const W* e = ch + g * K;
+      W t[K / 2], o[K / 2];
+#pragma unroll
+      for (int i = 0; i < K / 2; ++i) t[i] = take[(g * K / 2 + i) * kCols];
+      if (half) pt_last<K / 2, K>(e + K / 2, t, o, q);
+      else pt_last<0, K / 2>(e, t, o, q);
+      if (grp * G + g < P.nprod) pt_put<K / 2>(P.c + off[g] + (size_t)K * j + half * (K / 2), o);
+    }
   }
 }
 
-// 32-bit words: three waves per SIMD fit the registers (64 point words per thread); 64-bit
-// words: two.
-template <typename W, int L, int LK>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(W) == 4 ? 3 : 2, sizeof(W) == 4 ? 3 : 2)))
+// Two halves per workgroup.  A thread then holds one operand's 32 points, 32-bit words fit 128
+// registers and four waves per SIMD; 64-bit words run at two.  Against one half with both
+// operands (three waves per SIMD), us: n = 4096, 8 products 18.0 -> 14.2, 2048 products 83 -> 82;
+// n = 16384, 48 products 46.7 -> 43.5; 64-bit n = 4096, one product 50 -> 38, 1024 166 -> 161.
+template <typename W, int L, int LK, int C>
+__global__ __launch_bounds__(512 * C)
+__attribute__((amdgpu_waves_per_eu(sizeof(W) == 4 ? 4 : 2, sizeof(W) == 4 ? 4 : 2)))
 void ptrans_kernel(const PtParams<W> P) {
   extern __shared__ __align__(16) uint8_t smem[];
-  pt_group<W, L, LK>(P, blockIdx.x, smem);
+  pt_group<W, L, LK, C, 2>(P, blockIdx.x, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -520,7 +601,8 @@ __global__ __launch_bounds__(256) void pt_outer_inverse_kernel(const PtOuter<W> 
   }
   pt_stages<2, -1, K>(ch, q, yhigh);
   pt_stages<2, -1, K>(ch + K, q, yhigh);
-  pt_last<LK, 0>(ch, ch + K, c, q, yhigh);
+  pt_twist<LK, 0>(ch + K, q, yhigh);
+  pt_last<0, K>(ch, ch + K, c, q);
   pt_put<K>(P.c + (p * kPtOuterM + j) * K, c);
 }
 

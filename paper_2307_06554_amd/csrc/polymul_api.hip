@@ -285,7 +285,7 @@ template <int L, typename W, int WPE> const void* k_stream() { return (const voi
 template <typename W> const void* k_stream8() { return (const void*)stream8_kernel<W>; }
 const void* k_grouped() { return (const void*)grouped_kernel; }
 template <int L> const void* k_shared() { return (const void*)mfma32_shared_kernel<L>; }
-template <typename W, int L, int LK> const void* k_ptrans() { return (const void*)ptrans_kernel<W, L, LK>; }
+template <typename W, int L, int LK, int C> const void* k_ptrans() { return (const void*)ptrans_kernel<W, L, LK, C>; }
 template <int L, bool SHB> const void* k_small() { return (const void*)mfma16_group_kernel<L, SHB>; }
 
 template <int L, bool SMALL>
@@ -582,14 +582,18 @@ polymul_status run_stream(const W* a, const W* b, W* c, uint32_t n, const uint64
 // window covers as it is.
 bool ptrans_modulus(uint32_t q) { return (q & 1) && q >= 3 && q <= (uint32_t)limb_top(4); }
 
-// `points`: the transform's points, the outer one's included (their inverse goes into rc).
-bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points) {
+// Degree bound of the sub-products of a transform of degree n.
+uint32_t ptrans_m(uint64_t n) { return n > 4096 ? 512 : 256; }
+
+// `points`: the transform's points, the outer one's included (their inverse goes into rc);
+// M: the sub-products' degree bound.
+bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points, uint32_t M) {
   pm = PtMod32{};
   pm.m = make_mod32(q, L);
   uint32_t inv = q;  // Newton: doubles the correct low bits, three to begin with
   for (int i = 0; i < 5; ++i) inv *= 2 - q * inv;
   pm.qinv = inv;
-  pm.lift = (uint64_t)q * ((uint64_t)L * L * kPtM << 13);
+  pm.lift = (uint64_t)q * ((uint64_t)L * L * M << 13);
   // 2^32 / points mod q, halving with the odd q
   uint64_t f = ((uint64_t)1 << 32) % q;
   for (uint32_t p = points; p > 1; p /= 2) f = f & 1 ? (f + q) / 2 : f / 2;
@@ -600,7 +604,7 @@ bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points) {
   return true;
 }
 // False when a constant of this modulus does not split into two signed words.
-bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {
+bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {  // M = 256
   pm = PtMod64{};
   pm.m = make_mod64(q, L);
   uint64_t inv = q;
@@ -629,13 +633,14 @@ bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {
   return true;
 }
 
-template <typename W, int L, int LK>
+template <typename W, int L, int LK, int C = 1>
 polymul_status launch_ptrans(const PtParams<W>& P, hipStream_t s) {
-  if (allow_lds<k_ptrans<W, L, LK>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
+  if (allow_lds<k_ptrans<W, L, LK, C>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
   constexpr uint32_t G = 16 >> LK;
   const uint64_t groups = (P.nprod + G - 1) / G;
   if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
-  hipLaunchKernelGGL((ptrans_kernel<W, L, LK>), dim3((uint32_t)groups), dim3(kThreads), (pt_lds_bytes<W, L>()), s, P);
+  hipLaunchKernelGGL((ptrans_kernel<W, L, LK, C>), dim3((uint32_t)groups), dim3(512 * C), (pt_lds_bytes<W, L, C, 2>()), s,
+                     P);
   return launch_status();
 }
 template <typename W, int L>
@@ -643,29 +648,37 @@ polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
   switch (P.n) {
     case 1024: return launch_ptrans<W, L, 2>(P, s);
     case 2048: return launch_ptrans<W, L, 3>(P, s);
-    default: return launch_ptrans<W, L, 4>(P, s);
+    case 4096: return launch_ptrans<W, L, 4>(P, s);
   }
+  if constexpr (sizeof(W) == 4) return launch_ptrans<W, L, 4, 2>(P, s);
+  return POLYMUL_EINVAL;
 }
 
-// 32-bit words: n = 1024 .. 4096 unless a tile side was asked for.
+// 32-bit words: n = 1024 .. 8192 unless a tile side was asked for.
 bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L) {
-  if (n < 1024 || n > 4096) return false;
+  if (n < 1024 || n > 8192) return false;
   if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;
   for (uint32_t i = 0; i < lc; ++i)
     if (!ptrans_modulus(qs[i])) return false;
   return true;
 }
 
-polymul_status run_ptrans(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
-                          uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, hipStream_t s,
-                          uint32_t lrep, bool b_shared, uint32_t outer_points = 1) {
-  PtParams<uint32_t> P{};
+void fill_ptrans(PtParams<uint32_t>& P, const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n,
+                 const uint32_t* qs, uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, uint32_t lrep,
+                 bool b_shared, uint32_t outer_points) {
+  P = PtParams<uint32_t>{};
   P.a = a; P.b = b; P.c = c;
   P.nprod = nprod;
   P.n = n;
   P.lc = lc; P.nq_total = nq_total; P.l0 = l0; P.lrep = lrep;
   P.b_shared = b_shared ? 1u : 0u;
-  for (uint32_t i = 0; i < lc; ++i) fill_ptmod(P.mods[i], qs[i], L, 2 * n / kPtM * outer_points);
+  for (uint32_t i = 0; i < lc; ++i) fill_ptmod(P.mods[i], qs[i], L, 2 * n / ptrans_m(n) * outer_points, ptrans_m(n));
+}
+polymul_status run_ptrans(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
+                          uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, hipStream_t s,
+                          uint32_t lrep, bool b_shared, uint32_t outer_points = 1) {
+  PtParams<uint32_t> P;
+  fill_ptrans(P, a, b, c, n, qs, lc, nq_total, l0, nprod, L, lrep, b_shared, outer_points);
   switch (L) {
     case 2: return launch_ptrans_L<uint32_t, 2>(P, s);
     case 3: return launch_ptrans_L<uint32_t, 3>(P, s);
@@ -686,7 +699,7 @@ bool fill_ptrans64(PtParams<uint64_t>& P, const uint64_t* a, const uint64_t* b, 
   P.n = n;
   P.lc = 1; P.nq_total = 1; P.l0 = 0; P.lrep = 1;
   P.b_shared = b_shared ? 1u : 0u;
-  return fill_ptmod(P.mods[0], q, *L, 2 * n / kPtM * outer_points);
+  return fill_ptmod(P.mods[0], q, *L, 2 * n / ptrans_m(n) * outer_points);
 }
 polymul_status launch_ptrans64(const PtParams<uint64_t>& P, int L, hipStream_t s) {
   switch (L) {
@@ -863,10 +876,8 @@ polymul_status run_rns_karatsuba(const uint32_t* a, const uint32_t* b, uint32_t*
     bool odd = true;
     for (uint32_t l = 0; l < L; ++l) odd = odd && ptrans_modulus(q[l]);
     const int Lq = limbs32(q, L);
-    // at n = 8192 two Karatsuba levels (nine sub-products of degree 2048 on the transform) are
-    // ahead: 128 against 165 us for 512 products
     if (odd && n > 8192) return run_outer32(a, b, c, n, q, L, batch, workspace, stream);
-    if (odd && n <= 4096 && ptrans_takes((uint32_t)n, q, L, Lq))
+    if (odd && n <= 8192 && ptrans_takes((uint32_t)n, q, L, Lq))
       return run_ptrans(a, b, c, (uint32_t)n, q, L, L, 0, batch * L, Lq, stream, 1, false);
   }
   const uint32_t nsub = depth == 1 ? 3 : depth == 2 ? 9 : 27;

@@ -34,7 +34,7 @@ def check(got, want, what):
     assert np.array_equal(got, want), what + ": " + mismatch_report(got, want)
 
 
-@pytest.mark.parametrize("n", [1024, 2048, 4096])
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
 @pytest.mark.parametrize("q", [3, 257, 3329, 32639, 32641, 65537, 8355711, 8355713, 16777213, Q30, Q_TOP, Q_TOP + 2,
                                Q30 - 1])
 def test_moduli(n, q):
@@ -45,7 +45,7 @@ def test_moduli(n, q):
         check(got, oracle.negacyclic(a, b, q), f"n={n}, q={q}, batch {batch}")
 
 
-@pytest.mark.parametrize("n", [1024, 2048, 4096])
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
 def test_channels_and_shared_operand(n):
     rng = np.random.default_rng(n)
     qs = [Q30, 12289, Q_TOP] + [Q30 + 2 * i for i in range(1, 16)]  # 18: two launches
