@@ -113,7 +113,9 @@ polymul_status polymul_negacyclic_plain(const uint32_t* a, const uint32_t* b, ui
  * queue counters (left at zero by every launch), the graph and, when it cuts
  * large items along K into runs (items that would take more than an even share
  * of the work), the buffer the runs leave their residues in and the table of
- * the sums that one more launch forms from them.  Pointers are baked in: later executes read
+ * the sums that one more launch forms from them; 32-bit groups of degree 8192 on
+ * the polynomial transform use the same buffer for their sub-products, which one
+ * launch per group puts together.  Pointers are baked in: later executes read
  * and write the same buffers.  A plan must not be executed concurrently with
  * itself.  flags: 0, or POLYMUL_PLAN_NO_GRAPH to launch directly each time.
  */

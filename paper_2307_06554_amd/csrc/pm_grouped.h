@@ -5,18 +5,21 @@
 // with that order approximates longest-processing-time-first).  Resident groups
 // run with as many int8 limbs as their modulus needs.  Each item is a
 // group of four 32x32 tiles of LDS-resident products (degrees 4..4096), a group
-// of products on 16x16 tiles (64..512, where the tile table says so) or one
-// 64x64 block of a K-streamed product (every other degree).  Algorithm 1's
+// of products on 16x16 tiles (64..512, where the tile table says so), 4096 / n products
+// through the polynomial transform (1024..4096, and the three sub-products of a Karatsuba level
+// on each product of 8192) or one 64x64 block of a K-streamed
+// product (every other degree).  Algorithm 1's
 // GenConfig / ExtractDimensions run once on the host when the plan is built;
 // the launch only reads the resulting job table.
 #pragma once
 #include "pm_mfma32.h"
 #include "pm_mfma16.h"
+#include "pm_ptrans.h"
 #include "pm_stream.h"
 
 namespace pm {
 
-enum : uint32_t { kJobResident = 0, kJobStream = 1, kJobSmall = 2 };
+enum : uint32_t { kJobResident = 0, kJobStream = 1, kJobSmall = 2, kJobPtrans = 3 };
 
 struct GroupJob {
   uint32_t kind;
@@ -24,12 +27,13 @@ struct GroupJob {
   uint32_t pad[2];
   Mfma32Params rp;   // kind == kJobResident, or kJobSmall (16x16 tiles, rp.slots products per item)
   StreamParams sp;   // kind == kJobStream (4 limbs)
+  PtParams<uint32_t> pp;  // kind == kJobPtrans (4 limbs, 4096 / n products per item)
 };
 
 struct WorkItem {
   uint32_t group;    // index into the GroupJob table
   uint32_t index;    // resident: tile-group index; small: group of rp.slots products;
-                     // stream: product * ublocks + u-block
+                     // stream: product * ublocks + u-block; transform: group of 4096 / n products
 };
 
 template <int L>
@@ -75,6 +79,12 @@ void grouped_kernel(const GroupJob* __restrict__ jobs, const WorkItem* __restric
         case 2: small_item<2>(job.rp, w.index, smem); break;
         case 3: small_item<3>(job.rp, w.index, smem); break;
         default: small_item<4>(job.rp, w.index, smem); break;
+      }
+    } else if (job.kind == kJobPtrans) {
+      switch (job.pp.n) {
+        case 1024: pt_group<uint32_t, 4, 2, 1, 1>(job.pp, w.index, smem); break;
+        case 2048: pt_group<uint32_t, 4, 3, 1, 1>(job.pp, w.index, smem); break;
+        default: pt_group<uint32_t, 4, 4, 1, 1>(job.pp, w.index, smem); break;
       }
     } else {
       stream_block<4, uint32_t>(job.sp, w.index, smem);

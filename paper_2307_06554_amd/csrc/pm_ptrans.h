@@ -96,6 +96,7 @@ struct PtParams {
   uint32_t n;
   uint32_t lc, nq_total, l0, lrep;  // products and moduli as in Mfma32Params
   uint32_t b_shared;
+  uint32_t kara;  // plans, n = 4096: product p is sub-product p % 3 of one Karatsuba level on product p / 3
   typename PtModOf<W>::Mod mods[PtModOf<W>::kMods];
 };
 
@@ -409,6 +410,21 @@ __device__ __forceinline__ void pt_put(W* p, const W* x) {
   }
 }
 
+// Sub-operand d of one Karatsuba level (pm_karatsuba.h): the even words, the odd ones or their sums.
+template <int K>
+__device__ __forceinline__ void pt_load_kara(const uint32_t* p, uint32_t d, const ModQ32& m, uint32_t* x) {
+#pragma unroll
+  for (int i = 0; i < K; i += 2) {
+    uint32_t t[4];
+    pt_load<4>(p + 2 * i, t);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const uint32_t e = reduce_u32(t[2 * k], m), o = reduce_u32(t[2 * k + 1], m);
+      x[i + k] = d == 0 ? e : d == 1 ? o : pt_add(e, o, m.q);
+    }
+  }
+}
+
 // One workgroup of 4 C H waves: G = 16 / K products of degree bound K 256 C.  Wave: half, c, w
 // (w the lowest two bits); a thread owns column 16 c + 4 w + row of the rows of 16 C.  H = 1: it
 // holds both operands' points.  H = 2: half 0 transforms a and, in the end, the even points,
@@ -435,6 +451,15 @@ __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uin
       off[g] = wave_uniform(gp * P.n);
       const uint64_t boff = wave_uniform(b_product(P, gp, li[g]) * P.n);
       li[g] = wave_uniform(li[g]);
+      if constexpr (H == 1 && G == 1 && sizeof(W) == 4) {
+        if (P.kara) {
+          const uint64_t first = wave_uniform(gp / 3 * 2 * P.n);
+          const uint32_t d = wave_uniform((uint32_t)(gp % 3));
+          pt_load_kara<K>(P.a + first + (size_t)2 * K * j, d, P.mods[0].m, x[0]);
+          pt_load_kara<K>(P.b + first + (size_t)2 * K * j, d, P.mods[0].m, x[OPS - 1]);
+          continue;
+        }
+      }
       if constexpr (H == 1) {
         pt_load<K>(P.a + off[g] + (size_t)K * j, x[0] + g * K);
         pt_load<K>(P.b + boff + (size_t)K * j, x[OPS - 1] + g * K);

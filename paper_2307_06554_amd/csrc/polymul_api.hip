@@ -967,6 +967,7 @@ struct polymul_plan {
   uint32_t* d_counter = nullptr;    // queue counter and workgroups-left counter (zero between launches)
   void* d_part_ws = nullptr;        // residues of K-split runs
   std::vector<SplitSeg> segs;       // K-split jobs: c = sum of their runs mod q, one launch for all
+  std::vector<KaraParams> kara;     // n = 8192 groups on the transform: c from three sub-products
   SplitSeg* d_segs = nullptr;
   uint32_t sum_blocks = 0;
   uint32_t nitems = 0;
@@ -1003,6 +1004,10 @@ polymul_status plan_launch(const polymul_plan* p, hipStream_t s) {
       st = launch_status();
       if (st != POLYMUL_OK) return st;
     }
+    for (const KaraParams& k : p->kara) {
+      st = kara_combine(k, 1, (k.nprod * k.np + 255) / 256, s);
+      if (st != POLYMUL_OK) return st;
+    }
   }
   for (size_t i = 0; i < p->wide.size(); ++i) {
     polymul_status st = p->wide_L[i] == 4 ? launch_stream_L<4, uint64_t, 2>(p->wide[i], p->wide_lds[i], s)
@@ -1032,9 +1037,25 @@ void plan_free(polymul_plan* p) {
 std::atomic<uint32_t> g_plan_share_pct{140};
 std::atomic<uint32_t> g_plan_stream_pct{125};
 
+// A plan's 32-bit group goes through the polynomial transform where its calls would, at four limbs
+// (moduli above 2^24: the others' tiles do a quarter or half of the matrix work).  An item of
+// 4096 / n products takes about as long as 5632 MFMAs of a tile group (20-26 us with a second
+// workgroup on its CU, where a group of n = 4096 with 8192 takes 38 us).  A product of n = 8192 is
+// three items, the sub-products of one Karatsuba level, and a share of the combine kernel: as
+// K-split runs on tiles it took four of 33 us, the last items of the uneven batch by far.  The
+// sub-products live in the plan's buffer (1.5 times c), so groups that would need more than
+// 256 MiB of it stay on the tiles.
+bool plan_ptrans(uint32_t n, uint64_t count, uint32_t q, int L) {
+  if (n == 8192 && count > (256u << 20) / (3 * 4096 * 4)) return false;
+  return L == 4 && ptrans_takes(n, &q, 1, L);
+}
+constexpr uint64_t kPtItemCost = 5632;
+uint64_t plan_ptrans_items(uint32_t n, uint64_t count) { return n == 8192 ? 3 * count : (count * n + 4095) / 4096; }
+
 // Estimated time of one item (MFMAs per wave of its four tiles, the streamed
 // blocks' weighted), for the largest-first order and the split decision.
 uint64_t item_cost(const GroupJob& j) {
+  if (j.kind == kJobPtrans) return kPtItemCost;
   if (j.kind == kJobSmall) {  // slots x tiles x K-steps of L^2 MFMAs of half the length
     const uint64_t steps = j.rp.n >> 6;
     return (uint64_t)j.rp.slots * (1u << j.rp.log2U) * steps * j.L * j.L / 2;
@@ -1050,8 +1071,11 @@ uint64_t item_cost(const GroupJob& j) {
 // The same for one unsplit item of a 32-bit group on its default route (resident for
 // n in [4, 8192]: beyond 4096 only as K-split runs, else streamed), and the number of
 // such items.
-void default_cost(uint32_t n, uint64_t count, int L, uint64_t* items, uint64_t* cost) {
-  if (n >= 64 && plan_tile(n, L) == 16) {
+void default_cost(uint32_t n, uint32_t q, uint64_t count, int L, uint64_t* items, uint64_t* cost) {
+  if (plan_ptrans(n, count, q, L)) {
+    *items = plan_ptrans_items(n, count);
+    *cost = kPtItemCost;
+  } else if (n >= 64 && plan_tile(n, L) == 16) {
     const Geometry32 g = geometry32(n, 16);
     const uint32_t slots = plan_small_slots((uint32_t)L * (g.a_plane + g.b_plane));
     *items = (count + slots - 1) / slots;
@@ -1206,7 +1230,7 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
     if (groups[g].elem_bytes != 4 || groups[g].count == 0) continue;
     const uint32_t q32 = (uint32_t)groups[g].q;
     uint64_t ni, ci;
-    default_cost((uint32_t)groups[g].n, groups[g].count, limbs32(&q32, 1), &ni, &ci);
+    default_cost((uint32_t)groups[g].n, q32, groups[g].count, limbs32(&q32, 1), &ni, &ci);
     total_cost += ni * ci;
   }
   const uint64_t share = std::max<uint64_t>(
@@ -1233,10 +1257,29 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
     polymul_status st;
     uint64_t ni, ci;
     const int Lg = limbs32(&q32, 1);
-    default_cost(n, G.count, Lg, &ni, &ci);
+    default_cost(n, q32, G.count, Lg, &ni, &ci);
     const bool split = ci > share;
     job.L = (uint32_t)Lg;
-    if (n >= 64 && plan_tile(n, Lg) == 16) {
+    if (plan_ptrans(n, G.count, q32, Lg)) {
+      job.kind = kJobPtrans;
+      if (n == 8192) {
+        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, nullptr, 4096, &q32, 1, 1, 0, 3 * G.count, Lg, 1,
+                    false, 1);
+        job.pp.kara = 1;
+        job.pp.c = (uint32_t*)(uintptr_t)part_words;  // an offset until the buffer exists
+        part_words += 3 * G.count * 4096;
+        KaraParams K{};
+        K.c = (uint32_t*)G.c;
+        K.nprod = G.count; K.n = n; K.np = 4096; K.depth = 1; K.nsub = 3; K.L = 1;
+        K.mods[0] = make_mod32(q32, Lg);
+        p->kara.push_back(K);
+      } else {
+        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0, G.count, Lg, 1,
+                    false, 1);
+      }
+      lds = pt_lds_bytes<uint32_t, 4, 1, 1>();
+      st = POLYMUL_OK;
+    } else if (n >= 64 && plan_tile(n, Lg) == 16) {
       job.kind = kJobSmall;
       st = fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
                        G.count, Lg, 16, &lds);
@@ -1277,7 +1320,8 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
     if (st != POLYMUL_OK) { plan_free(p); return st; }
     p->lds = std::max(p->lds, lds);
     const uint32_t jid = (uint32_t)jobs.size();
-    const uint64_t cnt = job.kind == kJobSmall      ? (G.count + job.rp.slots - 1) / job.rp.slots
+    const uint64_t cnt = job.kind == kJobPtrans     ? ni
+                         : job.kind == kJobSmall    ? (G.count + job.rp.slots - 1) / job.rp.slots
                          : job.kind == kJobResident ? ((G.count << job.rp.log2U) + 3) / 4 * job.rp.kparts
                                                     : G.count * job.sp.ublocks * job.sp.kparts;
     if (cnt + items.size() > 0xFFFFFFFFull) { plan_free(p); return POLYMUL_EUNSUPPORTED; }
@@ -1301,7 +1345,12 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
         plan_free(p);
         return POLYMUL_ENOMEM;
       }
+      size_t nk = 0;
       for (GroupJob& j : jobs) {
+        if (j.kind == kJobPtrans && j.pp.kara) {
+          j.pp.c = (uint32_t*)p->d_part_ws + (uintptr_t)j.pp.c;
+          p->kara[nk++].sc = j.pp.c;
+        }
         if (j.kind == kJobStream && j.sp.kparts > 1) {
           j.sp.part_ws = (uint32_t*)p->d_part_ws + (uintptr_t)j.sp.part_ws;
           p->segs.push_back({(const uint32_t*)j.sp.part_ws, (uint32_t*)j.sp.c, j.sp.nprod * j.sp.n, j.sp.kparts,

@@ -141,3 +141,24 @@ def test_direct_call_in_chunks_and_on_another_stream(monkeypatch):
         got = pm.polymul_negacyclic_u64(da, db, GOLDILOCKS)
     s.synchronize()
     check(to_host(got, np.uint64), want, "current stream")
+
+
+def test_plan_groups():
+    """Plan items on the transform: full and ragged items of every degree, two groups of n = 8192 (their
+    sub-products share the plan's buffer), moduli that stay on the tiles beside them, replays."""
+    rng = np.random.default_rng(9)
+    shapes = [(1024, 5, Q30), (1024, 4, Q_TOP), (2048, 3, Q30 + 2), (4096, 2, Q30), (8192, 2, Q30), (8192, 1, Q_TOP),
+              (8192, 1, Q30 - 1), (4096, 1, 12289), (2048, 1, Q_TOP + 2), (256, 9, Q30)]
+    operands = [edge_operands(rng, count, n, q) for n, count, q in shapes]
+    operands[4][0][1] = draw(rng, 8192, 1 << 32)  # words outside [0, q) through the Karatsuba level
+    held = [(to_dev(a), to_dev(b), to_dev(np.full_like(a, 7)), n, q) for (a, b), (n, _, q) in zip(operands, shapes)]
+    want = [oracle.negacyclic(a, b, q) for (a, b), (_, _, q) in zip(operands, shapes)]
+    for flags in (0, 1):
+        plan = pm.Plan(held, flags)
+        for _ in range(2):
+            for g in held:
+                g[2].fill_(-1)
+            plan.execute()
+            for g, w in zip(held, want):
+                check(to_host(g[2], np.uint32), w, f"n={g[3]}, q={g[4]}, flags {flags}")
+        plan.close()
