@@ -57,6 +57,9 @@ __device__ __forceinline__ void small_item(const Mfma32Params& P, uint32_t index
 // to leave sets both back to zero, so that the next launch (a graph replay) starts
 // from an empty queue without a reset node.  Every workgroup's final claim has
 // returned before it counts itself out, so no claim can follow the reset.
+// PT: the list has transform items.  Plans without them run the kernel without that code, whose
+// registers spill beside it (a plan of small degrees: 23.6 against 24.2 us per replay).
+template <bool PT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void grouped_kernel(const GroupJob* __restrict__ jobs, const WorkItem* __restrict__ items, uint32_t nitems,
                     uint32_t* counter) {
@@ -80,8 +83,8 @@ void grouped_kernel(const GroupJob* __restrict__ jobs, const WorkItem* __restric
         case 3: small_item<3>(job.rp, w.index, smem); break;
         default: small_item<4>(job.rp, w.index, smem); break;
       }
-    } else if (job.kind == kJobPtrans) {
-      switch (job.pp.n) {
+    } else if (PT && job.kind == kJobPtrans) {
+      if constexpr (PT) switch (job.pp.n) {
         case 1024: pt_group<uint32_t, 4, 2, 1, 1>(job.pp, w.index, smem); break;
         case 2048: pt_group<uint32_t, 4, 3, 1, 1>(job.pp, w.index, smem); break;
         default: pt_group<uint32_t, 4, 4, 1, 1>(job.pp, w.index, smem); break;

@@ -283,7 +283,7 @@ polymul_status allow_lds() {
 template <int L, bool SMALL> const void* k_group() { return (const void*)mfma32_group_kernel<L, SMALL>; }
 template <int L, typename W, int WPE> const void* k_stream() { return (const void*)stream_kernel<L, W, WPE>; }
 template <typename W> const void* k_stream8() { return (const void*)stream8_kernel<W>; }
-const void* k_grouped() { return (const void*)grouped_kernel; }
+template <bool PT> const void* k_grouped() { return (const void*)grouped_kernel<PT>; }
 template <int L> const void* k_shared() { return (const void*)mfma32_shared_kernel<L>; }
 template <typename W, int L, int LK, int C> const void* k_ptrans() { return (const void*)ptrans_kernel<W, L, LK, C>; }
 template <int L, bool SHB> const void* k_small() { return (const void*)mfma16_group_kernel<L, SHB>; }
@@ -981,12 +981,13 @@ struct polymul_plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   bool use_graph = true;
+  bool transform = false;           // the work list has transform items
 };
 
 namespace {
 
 polymul_status plan_attrs() {
-  if (allow_lds<k_grouped>() != POLYMUL_OK) return POLYMUL_EDEVICE;
+  if (allow_lds<k_grouped<false>>() != POLYMUL_OK || allow_lds<k_grouped<true>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
   if (allow_lds<k_stream<4, uint64_t, 2>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
   if (allow_lds<k_stream8<uint64_t>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
   return POLYMUL_OK;
@@ -994,8 +995,12 @@ polymul_status plan_attrs() {
 
 polymul_status plan_launch(const polymul_plan* p, hipStream_t s) {
   if (p->nitems) {
-    hipLaunchKernelGGL(grouped_kernel, dim3(p->grid), dim3(kThreads), p->lds, s, p->d_jobs, p->d_items,
-                       p->nitems, p->d_counter);
+    if (p->transform)
+      hipLaunchKernelGGL(grouped_kernel<true>, dim3(p->grid), dim3(kThreads), p->lds, s, p->d_jobs, p->d_items,
+                         p->nitems, p->d_counter);
+    else
+      hipLaunchKernelGGL(grouped_kernel<false>, dim3(p->grid), dim3(kThreads), p->lds, s, p->d_jobs, p->d_items,
+                         p->nitems, p->d_counter);
     polymul_status st = launch_status();
     if (st != POLYMUL_OK) return st;
     if (!p->segs.empty()) {
@@ -1262,6 +1267,7 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
     job.L = (uint32_t)Lg;
     if (plan_ptrans(n, G.count, q32, Lg)) {
       job.kind = kJobPtrans;
+      p->transform = true;
       if (n == 8192) {
         fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, nullptr, 4096, &q32, 1, 1, 0, 3 * G.count, Lg, 1,
                     false, 1);
