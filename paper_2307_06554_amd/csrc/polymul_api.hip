@@ -646,7 +646,9 @@ polymul_status launch_ptrans(const PtParams<W>& P, hipStream_t s) {
 template <typename W, int L>
 polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
   switch (P.n) {
-    case 1024: return launch_ptrans<W, L, 2>(P, s);
+    case 1024:
+      if constexpr (L > 2) return launch_ptrans<W, L, 2>(P, s);
+      return POLYMUL_EINVAL;  // two limbs: on tiles (ptrans_takes)
     case 2048: return launch_ptrans<W, L, 3>(P, s);
     case 4096: return launch_ptrans<W, L, 4>(P, s);
   }
@@ -654,9 +656,14 @@ polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
   return POLYMUL_EINVAL;
 }
 
-// 32-bit words: n = 1024 .. 8192 unless a tile side was asked for.
-bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L) {
+// 32-bit words: n = 1024 .. 8192 unless a tile side was asked for.  At n = 1024, where the
+// transform only halves the matrix work, two limbs (a quarter of the limb products) stay on
+// tiles: 8192 products 48 us against 51, one product 8.0 against 9.4; and so do a few products
+// at three limbs: one 10.2 against 12.1, from 8 on the transform is level (13.0 against 13.1)
+// or ahead (8192: 69 against 80).
+bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L, uint64_t nprod) {
   if (n < 1024 || n > 8192) return false;
+  if (n == 1024 && (L == 2 || (L == 3 && nprod < 8))) return false;
   if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;
   for (uint32_t i = 0; i < lc; ++i)
     if (!ptrans_modulus(qs[i])) return false;
@@ -798,7 +805,7 @@ polymul_status run_mfma32(const uint32_t* a, const uint32_t* b, uint32_t* c, uin
     return POLYMUL_OK;
   }
   const int L = limbs32(qs, lc);
-  if (!cyclic && ptrans_takes(n, qs, lc, L))
+  if (!cyclic && ptrans_takes(n, qs, lc, L, nprod))
     return run_ptrans(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s, lrep, b_shared);
   Mfma32Params P;
   uint32_t lds;
@@ -877,7 +884,7 @@ polymul_status run_rns_karatsuba(const uint32_t* a, const uint32_t* b, uint32_t*
     for (uint32_t l = 0; l < L; ++l) odd = odd && ptrans_modulus(q[l]);
     const int Lq = limbs32(q, L);
     if (odd && n > 8192) return run_outer32(a, b, c, n, q, L, batch, workspace, stream);
-    if (odd && n <= 8192 && ptrans_takes((uint32_t)n, q, L, Lq))
+    if (odd && n <= 8192 && ptrans_takes((uint32_t)n, q, L, Lq, batch * L))
       return run_ptrans(a, b, c, (uint32_t)n, q, L, L, 0, batch * L, Lq, stream, 1, false);
   }
   const uint32_t nsub = depth == 1 ? 3 : depth == 2 ? 9 : 27;
@@ -1052,7 +1059,7 @@ std::atomic<uint32_t> g_plan_stream_pct{125};
 // 256 MiB of it stay on the tiles.
 bool plan_ptrans(uint32_t n, uint64_t count, uint32_t q, int L) {
   if (n == 8192 && count > (256u << 20) / (3 * 4096 * 4)) return false;
-  return L == 4 && ptrans_takes(n, &q, 1, L);
+  return L == 4 && ptrans_takes(n, &q, 1, L, count);
 }
 constexpr uint64_t kPtItemCost = 5632;
 uint64_t plan_ptrans_items(uint32_t n, uint64_t count) { return n == 8192 ? 3 * count : (count * n + 4095) / 4096; }
