@@ -216,15 +216,19 @@ __device__ __forceinline__ void pt_reduce(uint64_t* x, const ModQ64& m) {
   }
 }
 
-// The 2K points of one operand from its K words: the upper half of the transform's input is
-// zero, so its first stage only copies.
-template <int LK, typename W, typename M>
-__device__ __forceinline__ void pt_forward(W* x, W* v, const M& m, uint32_t yhigh) {
+// The 2K points of one operand from its K words in [0, q]: the upper half of the transform's
+// input is zero, so its first stage only copies.
+template <int LK, typename W>
+__device__ __forceinline__ void pt_points(const W* x, W* v, W q, uint32_t yhigh) {
   constexpr int K = 1 << LK;
-  pt_reduce<K>(x, m);
 #pragma unroll
   for (int p = 0; p < K; ++p) v[2 * p] = v[2 * p + 1] = x[pt_bitrev(p, LK)];
-  pt_stages<4, 1, 2 * K>(v, (W)m.q, yhigh);
+  pt_stages<4, 1, 2 * K>(v, q, yhigh);
+}
+template <int LK, typename W, typename M>
+__device__ __forceinline__ void pt_forward(W* x, W* v, const M& m, uint32_t yhigh) {
+  pt_reduce<(1 << LK)>(x, m);
+  pt_points<LK>(x, v, (W)m.q, yhigh);
 }
 
 // O_i <- w^(-i) O_i.
@@ -287,21 +291,31 @@ __device__ __forceinline__ void pt_store(uint8_t* base, uint32_t plane, uint32_t
 }
 
 // Four points of the column group's four columns into the digit planes of sub-product
-// `sub` (this row's): the reversed ext of a, or the rows of b.  brow: the columns' index / 16.
+// `sub` (this row's): the reversed ext of a, or the rows of b.  brow: the columns' index / 16;
+// cyclic: the sub-product is one of Z_q[y]/(y^M - 1), what wraps keeps its sign.
 template <int L, int C, bool IS_B, typename W, typename M>
-__device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const M& m, uint32_t wave, uint32_t brow) {
+__device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const M& m, uint32_t wave, uint32_t brow,
+                                                bool cyclic = false) {
   typedef PtGeom<C> G;
   W w[4] = {v[0], v[1], v[2], v[3]};
   pt_transpose(w);
   W pos[4], neg[4];
   if constexpr (IS_B) {
     pt_digits<L>(w, m, pos, neg);
+    if (cyclic) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) neg[i] = pos[i];
+    }
     uint8_t* rows = sub + L * G::kAPlane + 4 * wave;
     pt_store<L>(rows, G::kBPlane, (brow + G::kR - 1) * 16, pos);
     if (brow > 0) pt_store<L>(rows, G::kBPlane, (brow - 1) * 16, neg);
   } else {
     const W rev[4] = {w[3], w[2], w[1], w[0]};
     pt_digits<L>(rev, m, pos, neg);
+    if (cyclic) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) neg[i] = pos[i];
+    }
     const uint32_t off = G::kM - 4 - 4 * wave - 16 * brow;
     pt_store<L>(sub, G::kAPlane, off, pos);
     if (brow == G::kR - 1) pt_store<L>(sub, G::kAPlane, off + G::kM, neg);
@@ -380,6 +394,21 @@ __device__ __forceinline__ void pt_multiply(const uint8_t* sub, W* res, const PM
     out[e * kPtRow] = r;
     if (e == 3 && lane == 63 && tile == C - 1) res[(C - 1) * G::kColWords + 3 * kPtRow + 64] = (W)pm.m.q - r;
   }
+}
+
+// Where a thread's column is in a sub-product's results, and the column before it (times y:
+// -c[M - 1] before column 0).
+template <int C>
+__device__ __forceinline__ uint32_t pt_column(uint32_t c, uint32_t w, uint32_t row, uint32_t yhigh) {
+  return c * PtGeom<C>::kColWords + row * kPtRow + 16 * w + yhigh;
+}
+template <int C>
+__device__ __forceinline__ uint32_t pt_column_before(uint32_t c, uint32_t w, uint32_t row, uint32_t yhigh) {
+  typedef PtGeom<C> G;
+  return row > 0 ? pt_column<C>(c, w, row - 1, yhigh)
+         : w > 0 ? pt_column<C>(c, w - 1, 3, yhigh)
+         : c > 0 ? pt_column<C>(c - 1, 3, 3, yhigh)
+                 : (C - 1) * G::kColWords + 3 * kPtRow + (yhigh > 0 ? 48 + yhigh - 1 : 64);
 }
 
 // K consecutive words (K words or 16 bytes at a time, whichever is less).
@@ -474,13 +503,7 @@ __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uin
   }
 
   W* results = (W*)(smem + pt_results_at<W, L, C, H>());
-  // this thread's column of a sub-product's results, and the column before it (times y:
-  // -c[M - 1] before column 0)
-  const uint32_t cur = c * Geo::kColWords + row * kPtRow + 16 * w + yhigh;
-  const uint32_t prev = row > 0  ? cur - kPtRow
-                        : w > 0  ? c * Geo::kColWords + 3 * kPtRow + 16 * (w - 1) + yhigh
-                        : c > 0  ? (c - 1) * Geo::kColWords + 3 * kPtRow + 48 + yhigh
-                                 : (C - 1) * Geo::kColWords + 3 * kPtRow + (yhigh > 0 ? 48 + yhigh - 1 : 64);
+  const uint32_t cur = pt_column<C>(c, w, row, yhigh), prev = pt_column_before<C>(c, w, row, yhigh);
   // C^_s (1 +- y): of a product's points, the even ones first (H = 2: those of this half)
   W ch[kPtPoints / H];
 #pragma unroll
@@ -565,6 +588,222 @@ __attribute__((amdgpu_waves_per_eu(sizeof(W) == 4 ? 4 : 2, sizeof(W) == 4 ? 4 : 
 void ptrans_kernel(const PtParams<W> P) {
   extern __shared__ __align__(16) uint8_t smem[];
   pt_group<W, L, LK, C, 2>(P, blockIdx.x, smem);
+}
+
+// ---------------------------------------------------------------------------
+// The ring x^n - 1, n = K M: x^n - 1 = (x^(n/2) + 1)(x^(n/4) + 1) ... (x^M + 1)(x^M - 1).  The
+// factor x^(k M) + 1, 2 <= k <= K / 2, goes through the transform above with 2k points, the last
+// two are one product of degree M each: 2K - 2 sub-products, in the 2K slots that a product
+// of the other ring fills.  With D_k the product in the factor x^(k M) + 1 and D_0 that of
+// x^M - 1,
+//   c[t] = D_0[t mod M] / K + sum_k +-D_k[t mod k M] k / K, plus where t / M has bit k clear:
+// every D_k comes out of its transform scaled by 1/(2k), so 1/(2K) at the recombinations does
+// for all of them, D_1 and D_0 taken twice.
+// ---------------------------------------------------------------------------
+// LDS: both operands' residues (level k at words k M .. 2 k M of a product), or what the halves
+// swap and the products D (the same layout).
+template <int L, int C>
+constexpr uint32_t pt_cyclic_lds() {
+  const uint32_t b = pt_lds_bytes<uint32_t, L, C, 2>(), lin = 2 * 16 * 256 * C * 4;
+  return b > lin ? b : lin;
+}
+
+// Words t + M m of an operand, m < 2k, to its residues (words t + M m, m < k .. 1) in every factor,
+// at lin + M k; and back: s[m], m < 2k, from D_0 and the levels up to k.
+template <int k, int M>
+__device__ __forceinline__ void pt_cyclic_fold(uint32_t* y, uint32_t* lin, uint32_t q) {
+  if constexpr (k > 0) {
+#pragma unroll
+    for (int m = 0; m < k; ++m) {
+      lin[(k + m) * M] = pt_sub(y[m], y[m + k], q);
+      y[m] = pt_add(y[m], y[m + k], q);
+    }
+    pt_cyclic_fold<k / 2, M>(y, lin, q);
+  } else {
+    lin[0] = y[0];
+  }
+}
+template <int k, int M>
+__device__ __forceinline__ void pt_cyclic_unfold(uint32_t* s, const uint32_t* d, uint32_t q) {
+  if constexpr (k > 0) {
+    pt_cyclic_unfold<k / 2, M>(s, d, q);
+#pragma unroll
+    for (int m = 0; m < k; ++m) {
+      const uint32_t x = d[(k + m) * M];
+      s[m + k] = pt_sub(s[m], x, q);
+      s[m] = pt_add(s[m], x, q);
+    }
+  } else {
+    s[0] = d[0];
+  }
+}
+// Points of the levels k = 2^LK .. 2: 2k slots each, from slot v[0].
+template <int LK, int M>
+__device__ __forceinline__ void pt_cyclic_points(const uint32_t* lin, uint32_t j, uint32_t* v, uint32_t q, uint32_t yhigh) {
+  constexpr int K = 1 << LK;
+  if constexpr (LK > 0) {
+    uint32_t x[K];
+    pt_load<K>(lin + K * M + K * j, x);
+    pt_points<LK>(x, v, q, yhigh);
+    pt_cyclic_points<LK - 1, M>(lin, j, v + 2 * K, q, yhigh);
+  } else {
+    v[0] = lin[M + j];  // x^M + 1
+    v[1] = lin[j];      // x^M - 1
+    v[2] = v[3] = 0;    // no sub-product
+  }
+}
+// Index of even point `pt` within this half's words: the levels one after another, each in
+// bit-reversed order.
+template <int LK>
+__host__ __device__ constexpr int pt_cyclic_to(int pt) {
+  if constexpr (LK > 1)
+    return pt < (1 << LK) ? pt_bitrev(pt >> 1, LK - 1) : (1 << (LK - 1)) + pt_cyclic_to<LK - 1>(pt - (1 << LK));
+  else
+    return 0;  // x^M + 1 or x^M - 1
+}
+// This half's inverse stages of the levels k = 2^LK .. 2: it keeps its words at the start of each
+// level's and puts the other half's to `give`.
+template <int LK>
+__device__ __forceinline__ void pt_cyclic_inverse(uint32_t* e, uint32_t* give, uint32_t cols, uint32_t half, uint32_t q,
+                                                  uint32_t yhigh) {
+  if constexpr (LK > 0) {
+    constexpr int K = 1 << LK;
+    pt_stages<2, -1, K>(e, q, yhigh);
+    if (half) pt_twist<LK, 0>(e, q, yhigh);
+#pragma unroll
+    for (int i = 0; i < K / 2; ++i) {
+      const uint32_t lo = e[i], hi = e[K / 2 + i];
+      give[i * cols] = half ? lo : hi;
+      e[i] = half ? hi : lo;
+    }
+    pt_cyclic_inverse<LK - 1>(e + K, give + K / 2 * cols, cols, half, q, yhigh);
+  }
+}
+template <int LK, int M>
+__device__ __forceinline__ void pt_cyclic_last(const uint32_t* e, const uint32_t* take, uint32_t cols, uint32_t* lin, uint32_t j,
+                                               uint32_t half, uint32_t q) {
+  if constexpr (LK > 0) {
+    constexpr int K = 1 << LK;
+    uint32_t t[K / 2], o[K / 2];
+#pragma unroll
+    for (int i = 0; i < K / 2; ++i) t[i] = take[i * cols];
+    if (half) pt_last<K / 2, K>(e, t, o, q);
+    else pt_last<0, K / 2>(e, t, o, q);
+    pt_put<K / 2>(lin + K * M + K * j + half * (K / 2), o);
+    pt_cyclic_last<LK - 1, M>(e + K, take + K / 2 * cols, cols, lin, j, half, q);
+  }
+}
+
+// Workgroup, halves and columns as in pt_group<H = 2>.  The operands are folded, and the levels'
+// products put together, with a thread at words t + M m, all m < K: every word of global memory
+// is touched once, in whole rows; LDS hands the words over to the columns and back.  Bound as the
+// kernel above is.  Against the 32x32-tile kernel, four limbs, us: n = 2048, 1000 products 52.0 ->
+// 27.0, one 21.4 -> 13.7; n = 4096, 1024 products 188 -> 43; n = 8192, 512 products 392 -> 69.
+template <int L, int LK, int C>
+__global__ __launch_bounds__(512 * C) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void ptrans_cyclic_kernel(const PtParams<uint32_t> P) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  typedef PtGeom<C> Geo;
+  constexpr int K = 1 << LK, G = 16 >> LK, PTS = 2 * K, M = Geo::kM;
+  constexpr uint32_t kSub = Geo::template sub_bytes<L>();
+  const uint32_t lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
+  const uint32_t w = wave & 3, c = (wave >> 2) & (C - 1), half = wave / (4 * C);
+  const uint32_t yhigh = lane & 15, row = lane >> 4;
+  const uint32_t j = 16 * c + 4 * w + row + Geo::kR * yhigh, t = threadIdx.x & (M - 1);
+
+  uint64_t off[G];
+  uint32_t li[G];
+  uint32_t v[kPtPoints];
+  {
+    uint32_t* lin = (uint32_t*)smem + half * 16 * M;
+    uint32_t x[16];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint64_t p = (uint64_t)blockIdx.x * G + g;
+      const uint64_t gp = global_product(P, p < P.nprod ? p : P.nprod - 1, &li[g]);
+      off[g] = wave_uniform(gp * P.n);
+      li[g] = wave_uniform(li[g]);
+      const uint32_t* in = (half ? P.b : P.a) + off[g] + t;
+#pragma unroll
+      for (int m = 0; m < K; ++m) x[g * K + m] = in[m * M];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const ModQ32& mod = P.mods[li[g]].m;
+      uint32_t* y = x + g * K;
+      pt_reduce<K>(y, mod);
+      pt_cyclic_fold<K / 2, M>(y, lin + g * K * M + t, mod.q);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      pt_cyclic_points<LK - 1, M>(lin + g * K * M, j, v + g * PTS, P.mods[li[g]].m.q, yhigh);
+    __syncthreads();
+  }
+
+  uint32_t* results = (uint32_t*)(smem + pt_results_at<uint32_t, L, C, 2>());
+  const uint32_t cur = pt_column<C>(c, w, row, yhigh), prev = pt_column_before<C>(c, w, row, yhigh);
+  uint32_t ch[kPtPoints / 2];
+#pragma unroll
+  for (int ph = 0; ph < kPtPoints / kPtBatch; ++ph) {
+    const int g = ph * kPtBatch / PTS;  // the batch's product
+    const auto& pm = P.mods[li[g]];
+    const bool last = (ph + 1) * kPtBatch % PTS == 0;  // its end: x^M + 1, x^M - 1 and two idle slots
+#pragma unroll
+    for (int h = 0; h < kPtBatch; h += 4) {
+      uint8_t* sub = smem + (h + row) * kSub;
+      const bool cyclic = last && h == kPtBatch - 4 && row == 1;
+      if (half == 0) pt_stage_planes<L, C, false>(v + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c, cyclic);
+      else pt_stage_planes<L, C, true>(v + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c, cyclic);
+    }
+    __syncthreads();
+    if (!last || wave / C < kPtBatch - 2)
+      pt_multiply<L, C>(smem + wave / C * kSub, results + wave / C * Geo::kResWords, pm, lane, wave % C);
+    __syncthreads();
+    const uint32_t q = pm.m.q;
+#pragma unroll
+    for (int s = 0; s < kPtBatch; s += 2) {
+      const uint32_t* res = results + (s + half) * Geo::kResWords;
+      const int pt = (ph * kPtBatch + s) % PTS, to = g * K + pt_cyclic_to<LK>(pt);
+      if (pt == PTS - 2) continue;
+      const uint32_t x = res[cur];
+      if (pt == PTS - 4) {
+        ch[to] = pt_add(x, x, q);
+      } else {
+        const uint32_t y = res[prev];
+        ch[to] = pt_add(x, half ? q - y : y, q);
+      }
+    }
+  }
+
+  uint32_t* give = (uint32_t*)smem + half * 8 * M + t;
+  const uint32_t* take = (const uint32_t*)smem + (half ^ 1) * 8 * M + t;
+  uint32_t* lin = (uint32_t*)smem + 16 * M;
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    pt_cyclic_inverse<LK - 1>(ch + g * K, give + g * (K / 2) * M, M, half, P.mods[li[g]].m.q, yhigh);
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    pt_cyclic_last<LK - 1, M>(ch + g * K, take + g * (K / 2) * M, M, lin + g * K * M, j, half, P.mods[li[g]].m.q);
+    lin[(g * K + (half ? 0 : 1)) * M + j] = ch[g * K + K - 2];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const uint32_t q = P.mods[li[g]].m.q;
+    const uint32_t* d = lin + g * K * M + t;
+    uint32_t s[K / 2];
+    pt_cyclic_unfold<K / 4, M>(s, d, q);
+    if ((uint64_t)blockIdx.x * G + g < P.nprod) {
+      uint32_t* out = P.c + off[g] + half * (K / 2) * M + t;
+#pragma unroll
+      for (int m = 0; m < K / 2; ++m) {
+        const uint32_t x = d[(K / 2 + m) * M];
+        out[m * M] = pt_close<false>(s[m], half ? q - x : x, q);
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------

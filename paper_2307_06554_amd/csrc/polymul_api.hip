@@ -286,6 +286,7 @@ template <typename W> const void* k_stream8() { return (const void*)stream8_kern
 template <bool PT> const void* k_grouped() { return (const void*)grouped_kernel<PT>; }
 template <int L> const void* k_shared() { return (const void*)mfma32_shared_kernel<L>; }
 template <typename W, int L, int LK, int C> const void* k_ptrans() { return (const void*)ptrans_kernel<W, L, LK, C>; }
+template <int L, int LK, int C> const void* k_ptrans_cyclic() { return (const void*)ptrans_cyclic_kernel<L, LK, C>; }
 template <int L, bool SHB> const void* k_small() { return (const void*)mfma16_group_kernel<L, SHB>; }
 
 template <int L, bool SMALL>
@@ -693,6 +694,45 @@ polymul_status run_ptrans(const uint32_t* a, const uint32_t* b, uint32_t* c, uin
   }
 }
 
+// The ring x^n - 1, on the transform where the other ring is.  n = 1024, where two of a
+// product's eight slots are idle, takes it at four limbs from a workgroup's four products
+// on: one product 13.9 us against 13.2 on tiles, four 14.3 against 16.0, 4096 43 against 56; at
+// three limbs the two are level (13.4 and 13.4, 39.5 and 39.1).
+bool ptrans_takes_cyclic(uint32_t n, const uint32_t* qs, uint32_t lc, int L, uint64_t nprod) {
+  if (n == 1024 && (L < 4 || nprod < 4)) return false;
+  return ptrans_takes(n, qs, lc, L, nprod);
+}
+template <int L, int LK, int C = 1>
+polymul_status launch_ptrans_cyclic(const PtParams<uint32_t>& P, hipStream_t s) {
+  if (allow_lds<k_ptrans_cyclic<L, LK, C>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
+  constexpr uint32_t G = 16 >> LK;
+  const uint64_t groups = (P.nprod + G - 1) / G;
+  if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
+  hipLaunchKernelGGL((ptrans_cyclic_kernel<L, LK, C>), dim3((uint32_t)groups), dim3(512 * C), (pt_cyclic_lds<L, C>()), s, P);
+  return launch_status();
+}
+template <int L>
+polymul_status launch_ptrans_cyclic_L(const PtParams<uint32_t>& P, hipStream_t s) {
+  switch (P.n) {
+    case 1024:
+      if constexpr (L > 3) return launch_ptrans_cyclic<L, 2>(P, s);
+      return POLYMUL_EINVAL;  // on tiles (ptrans_takes_cyclic)
+    case 2048: return launch_ptrans_cyclic<L, 3>(P, s);
+    case 4096: return launch_ptrans_cyclic<L, 4>(P, s);
+  }
+  return launch_ptrans_cyclic<L, 4, 2>(P, s);
+}
+polymul_status run_ptrans_cyclic(const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n, const uint32_t* qs,
+                                 uint32_t lc, uint32_t nq_total, uint32_t l0, uint64_t nprod, int L, hipStream_t s) {
+  PtParams<uint32_t> P;
+  fill_ptrans(P, a, b, c, n, qs, lc, nq_total, l0, nprod, L, 1, false, 1);
+  switch (L) {
+    case 2: return launch_ptrans_cyclic_L<2>(P, s);
+    case 3: return launch_ptrans_cyclic_L<3>(P, s);
+    default: return launch_ptrans_cyclic_L<4>(P, s);
+  }
+}
+
 // 64-bit words, one modulus: parameters for degree n = 1024 .. 4096, or false where the
 // transform does not take the modulus.  Limb counts 4, 6 and 8 have kernels.
 bool fill_ptrans64(PtParams<uint64_t>& P, const uint64_t* a, const uint64_t* b, uint64_t* c, uint32_t n, uint64_t q,
@@ -807,6 +847,8 @@ polymul_status run_mfma32(const uint32_t* a, const uint32_t* b, uint32_t* c, uin
   const int L = limbs32(qs, lc);
   if (!cyclic && ptrans_takes(n, qs, lc, L, nprod))
     return run_ptrans(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s, lrep, b_shared);
+  if (cyclic && lrep == 1 && !b_shared && ptrans_takes_cyclic(n, qs, lc, L, nprod))
+    return run_ptrans_cyclic(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s);
   Mfma32Params P;
   uint32_t lds;
   polymul_status st =

@@ -1,7 +1,8 @@
 """The polynomial-transform route (32-bit words, odd moduli) word for word against
 the oracle: every transform size with full and ragged workgroups, moduli at the ends of its
 range and of each limb count's window, mixed moduli in one workgroup, words outside [0, q),
-the operands whose sums are largest, and a modulus just outside the range beside one inside."""
+the operands whose sums are largest, a modulus just outside the range beside one inside, and
+the ring x^n - 1."""
 import numpy as np
 import pytest
 
@@ -56,6 +57,16 @@ def test_channels_and_shared_operand(n):
     bs = np.ascontiguousarray(b[2])
     want = oracle.negacyclic_rns(a, np.ascontiguousarray(np.broadcast_to(bs, a.shape)), qs)
     check(to_host(pm.polymul_negacyclic_rns_shared(to_dev(a), to_dev(bs), qs), np.uint32), want, f"shared n={n}")
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+@pytest.mark.parametrize("q", [3, 257, 32639, 32641, 8355711, 8355713, Q30, Q_TOP, Q_TOP + 2, Q30 - 1])
+def test_cyclic_ring(n, q):
+    rng = np.random.default_rng([n, q, 1])
+    for batch in (1, 4, 7):  # 4: the smallest call on the route at 1024; 7: a ragged last workgroup
+        a, b = edge_operands(rng, batch, n, q)
+        got = to_host(pm.polymul_cyclic(to_dev(a), to_dev(b), q), np.uint32)
+        check(got, oracle.cyclic(a, b, q), f"n={n}, q={q}, batch {batch}")
 
 
 def test_a_tile_side_turns_the_route_off_with_the_same_result():
