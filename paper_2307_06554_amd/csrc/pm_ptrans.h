@@ -40,7 +40,7 @@
 // 64-bit words (one modulus, 4, 6 or 8 limbs): the same with 64-bit additions and a 64-bit
 // Montgomery step.  Sixteen products of n = 65536 with q = 2^64 - 2^32 + 1, through the outer
 // transform below: 3.03 ms on the streaming kernel, 1.41 ms through three Karatsuba levels,
-// 115 us here.
+// 108 us here.
 #pragma once
 #include "pm_mfma16.h"
 #include "pm_stream.h"
@@ -581,7 +581,7 @@ __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uin
 // Two halves per workgroup.  A thread then holds one operand's 32 points, 32-bit words fit 128
 // registers and four waves per SIMD; 64-bit words run at two.  Against one half with both
 // operands (three waves per SIMD), us: n = 4096, 8 products 18.0 -> 14.2, 2048 products 83 -> 82;
-// n = 16384, 48 products 46.7 -> 43.5; 64-bit n = 4096, one product 50 -> 38, 1024 166 -> 161.
+// n = 16384, 48 products 46.7 -> 43.5 (its outer kernels then as they were); 64-bit n = 4096, one product 50 -> 38, 1024 166 -> 161.
 template <typename W, int L, int LK, int C>
 __global__ __launch_bounds__(512 * C)
 __attribute__((amdgpu_waves_per_eu(sizeof(W) == 4 ? 4 : 2, sizeof(W) == 4 ? 4 : 2)))
@@ -812,11 +812,23 @@ void ptrans_cyclic_kernel(const PtParams<uint32_t> P) {
 // polynomials of degree 4096, the kernel above multiplies them (over a's points), an
 // inverse kernel puts the products together.  The work on the matrix units stays 2 n 512
 // multiply-adds whatever n is.  The forward and inverse kernels move 3 n and 5 n words per operand
-// and product (the inverse reads columns j and j - 1, the second from cache) and are bound
-// by memory; sixteen columns 256 apart share a row of lanes, so the rotations are again
-// row rotations.
+// and product (the inverse reads columns j and j - 1, the second from cache).
+//
+// Up to k0 = 4 a thread holds k0 columns j = ylow + (M / k0) h of all 2 k0 points: a power of w is
+// then a renaming of registers and a choice between addition and subtraction, and neighbouring lanes
+// have neighbouring columns.  k = 8 and 16 are R = k / 4 transforms of k0 = 4 (over i = R i1 + i0 at
+// fixed i0) and one step of radix R: with 2 k0 = 8,
+//   A^_(s + 8 m) = sum_{i0 < R} w^(8 i0 m) (w^(i0 s) U_i0[s]),  U_i0[s] = sum_i1 w^(R i1 s) A_(R i1 + i0),
+// the U's passing through LDS, where w^(i0 s) is an address; w^8 is -1 (R = 2) or y^(M/2) (R = 4).
+// The inverse is the same backwards.
+//
+// With the columns along rows of sixteen lanes instead (rotations by DPP, as above) a wave's access
+// was sixteen pieces of four words: forward and inverse took 18.0 and 16.6 us for sixteen products
+// of n = 65536 in 64-bit words, 12.2 and 7.5 us for 48 of n = 16384 in 32-bit words; now
+// 13.1 and 14.3, 9.3 and 4.3.  64 or 256 threads are no faster within the sequence of three launches.
 // ---------------------------------------------------------------------------
 constexpr int kPtOuterM = 4096;
+constexpr int kPtOuterThreads = 128;
 
 template <typename W> struct PtBase { typedef ModQ32 Mod; };
 template <> struct PtBase<uint64_t> { typedef ModQ64 Mod; };
@@ -832,42 +844,224 @@ struct PtOuter {
   typename PtBase<W>::Mod mods[PtModOf<W>::kMods];
 };
 
-// Block: product blockIdx.x / 16, 16 columns ylow of it (and their 16 yhigh each);
-// blockIdx.y: operand.
-template <typename W, int LK>
-__global__ __launch_bounds__(256) void pt_outer_forward_kernel(const PtOuter<W> P) {
-  constexpr int K = 1 << LK;
-  const uint64_t p = blockIdx.x >> 4;
-  const uint32_t yhigh = threadIdx.x & 15, j = ((blockIdx.x & 15) << 4) + (threadIdx.x >> 4) + 256 * yhigh;
-  const auto& m = P.mods[p % P.L];
-  W x[K], v[2 * K];
-  pt_load<K>((blockIdx.y ? P.b : P.a) + (p * kPtOuterM + j) * K, x);
-  pt_forward<LK>(x, v, m, yhigh);
-  W* out = (blockIdx.y ? P.sb : P.sa) + p * 2 * K * kPtOuterM + j;
+template <int LK>
+struct PtOuterGeom {
+  static constexpr int K = 1 << LK, LK0 = LK < 2 ? LK : 2, K0 = 1 << LK0, R = K / K0, S0 = 2 * K0;
+  static constexpr int B = kPtOuterM / K;                 // columns per step of w
+  static constexpr int Y = kPtOuterThreads / (R * R);     // of them per workgroup
+  static constexpr int kTiles = B / Y;                    // workgroups per product
+  static constexpr int kPart = S0 * K * Y + Y;            // words of one U_i0 in LDS (a row of Y more: i0 runs along lanes)
+  static constexpr int kHalves = R > 2 ? R / 2 : 1;       // columns M / 2 apart that w^8 joins
+  static constexpr int kUnits = S0 * (K / kHalves) / (R * R);  // (s, yhigh) pairs per thread, R > 1
+};
+
+// Column h of y^(ROT M / k0) z, as +-z[src].
+template <int K0, int ROT>
+struct PtTurn {
+  static constexpr int src(int h) { return (h - ROT) & (K0 - 1); }
+  static constexpr bool neg(int h) { return ((h - ROT) & K0) != 0; }
+};
+// (x, z) <- (x + Y z, x - Y z), Y = y^(ROT M / k0).
+template <int K0, int ROT, typename W>
+__device__ __forceinline__ void pt_reg_butterfly(W* x, W* z, W q) {
+  W s[K0], d[K0];
 #pragma unroll
-  for (int s = 0; s < 2 * K; ++s) out[s * kPtOuterM] = v[s];
+  for (int h = 0; h < K0; ++h) {
+    const W t = z[PtTurn<K0, ROT>::src(h)];
+    const W u = pt_add(x[h], t, q), v = pt_sub(x[h], t, q);
+    s[h] = PtTurn<K0, ROT>::neg(h) ? v : u;
+    d[h] = PtTurn<K0, ROT>::neg(h) ? u : v;
+  }
+#pragma unroll
+  for (int h = 0; h < K0; ++h) { x[h] = s[h]; z[h] = d[h]; }
+}
+// Decimation in time as in pt_stages, over v[N][K0].
+template <int S, int J, int DIR, int N, int K0, typename W>
+__device__ __forceinline__ void pt_reg_stage(W* v, W q) {
+  if constexpr (J < S / 2) {
+#pragma unroll
+    for (int b = 0; b < N; b += S)
+      pt_reg_butterfly<K0, DIR * J * (2 * K0 / S)>(v + (b + J) * K0, v + (b + J + S / 2) * K0, q);
+    pt_reg_stage<S, J + 1, DIR, N, K0>(v, q);
+  }
+}
+template <int S, int DIR, int N, int K0, typename W>
+__device__ __forceinline__ void pt_reg_stages(W* v, W q) {
+  if constexpr (S <= N) {
+    pt_reg_stage<S, 0, DIR, N, K0>(v, q);
+    pt_reg_stages<2 * S, DIR, N, K0>(v, q);
+  }
+}
+// c_i[h] = E_i + y^(-i M / k0) O_i in [0, q), into E.
+template <int K0, int I, typename W>
+__device__ __forceinline__ void pt_reg_last(W* e, const W* o, W q) {
+  if constexpr (I < K0) {
+#pragma unroll
+    for (int h = 0; h < K0; ++h) {
+      const W t = o[I * K0 + PtTurn<K0, -I>::src(h)];
+      e[I * K0 + h] = pt_close<false>(e[I * K0 + h], PtTurn<K0, -I>::neg(h) ? q - t : t, q);
+    }
+    pt_reg_last<K0, I + 1>(e, o, q);
+  }
+}
+
+// One step of radix R on t[R][kHalves] (R = 4: columns j and j + M / 2).  DIR -1: the inverse.
+template <int R, int DIR, typename W>
+__device__ __forceinline__ void pt_radix(W (&t)[R][R > 2 ? R / 2 : 1], W q) {
+  if constexpr (R == 2) {
+    const W x = t[0][0], z = t[1][0];
+    t[0][0] = pt_add(x, z, q);
+    t[1][0] = pt_sub(x, z, q);
+  } else {
+    W e0[2], e1[2], o0[2], o1[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      e0[h] = pt_add(t[0][h], t[2][h], q);
+      e1[h] = pt_sub(t[0][h], t[2][h], q);
+      o0[h] = pt_add(t[1][h], t[3][h], q);
+      o1[h] = pt_sub(t[1][h], t[3][h], q);
+    }
+    constexpr int P = DIR > 0 ? 1 : 3, N = 4 - P;  // t[P] = e1 + y^(M/2) o1, t[N] = e1 - y^(M/2) o1
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      t[0][h] = pt_add(e0[h], o0[h], q);
+      t[2][h] = pt_sub(e0[h], o0[h], q);
+      const W u = pt_add(e1[h], o1[1 - h], q), v = pt_sub(e1[h], o1[1 - h], q);
+      t[P][h] = h ? u : v;
+      t[N][h] = h ? v : u;
+    }
+  }
+}
+
+// Workgroup: one of kTiles column tiles of product blockIdx.x / kTiles; blockIdx.y: operand.
+template <typename W, int LK>
+__global__ __launch_bounds__(kPtOuterThreads) void pt_outer_forward_kernel(const PtOuter<W> P) {
+  typedef PtOuterGeom<LK> G;
+  constexpr int K = G::K, K0 = G::K0, R = G::R, S0 = G::S0, Y = G::Y;
+  const uint64_t p = blockIdx.x / G::kTiles;
+  const uint32_t tile = blockIdx.x % G::kTiles * Y;
+  const uint32_t i0 = threadIdx.x % R, ylow = threadIdx.x / R % Y, b = threadIdx.x / (R * Y);
+  const auto& m = P.mods[p % P.L];
+  const W q = (W)m.q;
+  const W* in = (blockIdx.y ? P.b : P.a) + p * kPtOuterM * K + (size_t)(tile + ylow + G::B * b) * K;
+  W* out = (blockIdx.y ? P.sb : P.sa) + p * 2 * K * kPtOuterM + tile;
+  W v[S0 * K0];
+  {
+    W x[K0 * K0];  // [h][i1]
+#pragma unroll
+    for (int h = 0; h < K0; ++h) {
+      if constexpr (R == 1) pt_load<K0>(in + (size_t)h * (kPtOuterM / K0) * K, x + h * K0);
+      else
+#pragma unroll
+        for (int i = 0; i < K0; ++i) x[h * K0 + i] = in[(size_t)h * (kPtOuterM / K0) * K + R * i + i0];
+    }
+    pt_reduce<K0 * K0>(x, m);
+#pragma unroll
+    for (int s = 0; s < K0; ++s)
+#pragma unroll
+      for (int h = 0; h < K0; ++h) v[2 * s * K0 + h] = v[(2 * s + 1) * K0 + h] = x[h * K0 + pt_bitrev(s, G::LK0)];
+  }
+  pt_reg_stages<4, 1, S0, K0>(v, q);
+  if constexpr (R == 1) {
+#pragma unroll
+    for (int s = 0; s < S0; ++s)
+#pragma unroll
+      for (int h = 0; h < K0; ++h) out[s * kPtOuterM + h * (kPtOuterM / K0) + ylow] = v[s * K0 + h];
+  } else {
+    __shared__ W lds[R * G::kPart];
+#pragma unroll
+    for (int s = 0; s < S0; ++s)
+#pragma unroll
+      for (int h = 0; h < K0; ++h) lds[i0 * G::kPart + (s * K + b + R * h) * Y + ylow] = v[s * K0 + h];
+    __syncthreads();
+    const uint32_t yl = threadIdx.x % Y;
+#pragma unroll
+    for (int u = 0; u < G::kUnits; ++u) {
+      const uint32_t unit = threadIdx.x / Y + u * R * R;
+      const int yh = (int)(unit % (K / G::kHalves)), s = (int)(unit / (K / G::kHalves));
+      W t[R][G::kHalves];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int h = 0; h < G::kHalves; ++h) {
+          const int from = yh + h * (K / 2) - i * s;
+          const W x = lds[i * G::kPart + (s * K + (from & (K - 1))) * Y + yl];
+          t[i][h] = i > 0 && (from & K) ? q - x : x;
+        }
+      pt_radix<R, 1>(t, q);
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int h = 0; h < G::kHalves; ++h)
+          out[(s + S0 * i) * kPtOuterM + G::B * (yh + h * (K / 2)) + yl] = t[i][h];
+    }
+  }
 }
 
 template <typename W, int LK>
-__global__ __launch_bounds__(256) void pt_outer_inverse_kernel(const PtOuter<W> P) {
-  constexpr int K = 1 << LK;
-  const uint64_t p = blockIdx.x >> 4;
-  const uint32_t yhigh = threadIdx.x & 15, j = ((blockIdx.x & 15) << 4) + (threadIdx.x >> 4) + 256 * yhigh;
+__global__ __launch_bounds__(kPtOuterThreads) void pt_outer_inverse_kernel(const PtOuter<W> P) {
+  typedef PtOuterGeom<LK> G;
+  constexpr int K = G::K, K0 = G::K0, R = G::R, S0 = G::S0, Y = G::Y;
+  const uint64_t p = blockIdx.x / G::kTiles;
+  const uint32_t tile = blockIdx.x % G::kTiles * Y;
+  const uint32_t i0 = threadIdx.x % R, ylow = threadIdx.x / R % Y, b = threadIdx.x / (R * Y);
   const W q = (W)P.mods[p % P.L].q;
   const W* in = P.sa + p * 2 * K * kPtOuterM;
-  const uint32_t prev = j ? j - 1 : kPtOuterM - 1;
-  W ch[2 * K], c[K];
+  // C^_s (1 +- y) at column j
+  const auto point = [&](int s, uint32_t j) {
+    const W x = in[s * kPtOuterM + j], y0 = in[s * kPtOuterM + (j ? j - 1 : kPtOuterM - 1)];
+    const W y = (j == 0) != ((s & 1) != 0) ? q - y0 : y0;
+    return pt_add(x, y, q);
+  };
+  W ch[S0 * K0];  // the even points, then the odd ones, in bit-reversed order
+  if constexpr (R == 1) {
 #pragma unroll
-  for (int s = 0; s < 2 * K; ++s) {
-    const W x = in[s * kPtOuterM + j], y0 = in[s * kPtOuterM + prev];
-    const W y = j ? y0 : q - y0;
-    ch[(s & 1) * K + pt_bitrev(s >> 1, LK)] = s & 1 ? pt_sub(x, y, q) : pt_add(x, y, q);
+    for (int s = 0; s < S0; ++s)
+#pragma unroll
+      for (int h = 0; h < K0; ++h)
+        ch[((s & 1) * K0 + pt_bitrev(s >> 1, G::LK0)) * K0 + h] = point(s, tile + ylow + h * (kPtOuterM / K0));
+  } else {
+    __shared__ W lds[R * G::kPart];
+    const uint32_t yl = threadIdx.x % Y;
+#pragma unroll
+    for (int u = 0; u < G::kUnits; ++u) {
+      const uint32_t unit = threadIdx.x / Y + u * R * R;
+      const int yh = (int)(unit % (K / G::kHalves)), s = (int)(unit / (K / G::kHalves));
+      W t[R][G::kHalves];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int h = 0; h < G::kHalves; ++h) t[i][h] = point(s + S0 * i, tile + yl + G::B * (yh + h * (K / 2)));
+      pt_radix<R, -1>(t, q);
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int h = 0; h < G::kHalves; ++h) {
+          const int to = yh + h * (K / 2) - i * s;
+          lds[i * G::kPart + (s * K + (to & (K - 1))) * Y + yl] = i > 0 && (to & K) ? q - t[i][h] : t[i][h];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < S0; ++s)
+#pragma unroll
+      for (int h = 0; h < K0; ++h)
+        ch[((s & 1) * K0 + pt_bitrev(s >> 1, G::LK0)) * K0 + h] = lds[i0 * G::kPart + (s * K + b + R * h) * Y + ylow];
   }
-  pt_stages<2, -1, K>(ch, q, yhigh);
-  pt_stages<2, -1, K>(ch + K, q, yhigh);
-  pt_twist<LK, 0>(ch + K, q, yhigh);
-  pt_last<0, K>(ch, ch + K, c, q);
-  pt_put<K>(P.c + (p * kPtOuterM + j) * K, c);
+  pt_reg_stages<2, -1, K0, K0>(ch, q);
+  pt_reg_stages<2, -1, K0, K0>(ch + K0 * K0, q);
+  pt_reg_last<K0, 0>(ch, ch + K0 * K0, q);
+  W* out = P.c + p * kPtOuterM * K + (size_t)(tile + ylow + G::B * b) * K;
+#pragma unroll
+  for (int h = 0; h < K0; ++h) {
+    W c[K0];
+#pragma unroll
+    for (int i = 0; i < K0; ++i) c[i] = ch[i * K0 + h];
+    if constexpr (R == 1) pt_put<K0>(out + (size_t)h * (kPtOuterM / K0) * K, c);
+    else
+#pragma unroll
+      for (int i = 0; i < K0; ++i) out[(size_t)h * (kPtOuterM / K0) * K + R * i + i0] = c[i];
+  }
 }
 
 }  // namespace pm

@@ -760,14 +760,15 @@ polymul_status launch_ptrans64(const PtParams<uint64_t>& P, int L, hipStream_t s
 // the workspace, 4 n words per product, the points' products over a's points.
 template <typename W, int LK>
 polymul_status launch_outer(const PtOuter<W>& P, uint64_t products, bool inverse, hipStream_t s) {
-  const dim3 grid((uint32_t)(products * 16), inverse ? 1 : 2);
-  if (inverse) hipLaunchKernelGGL((pt_outer_inverse_kernel<W, LK>), grid, dim3(256), 0, s, P);
-  else hipLaunchKernelGGL((pt_outer_forward_kernel<W, LK>), grid, dim3(256), 0, s, P);
+  const uint64_t groups = products * PtOuterGeom<LK>::kTiles;
+  if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
+  const dim3 grid((uint32_t)groups, inverse ? 1 : 2), threads(kPtOuterThreads);
+  if (inverse) hipLaunchKernelGGL((pt_outer_inverse_kernel<W, LK>), grid, threads, 0, s, P);
+  else hipLaunchKernelGGL((pt_outer_forward_kernel<W, LK>), grid, threads, 0, s, P);
   return launch_status();
 }
 template <typename W>
 polymul_status launch_outer_n(const PtOuter<W>& P, uint64_t n, uint64_t products, bool inverse, hipStream_t s) {
-  if (products * 16 > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
   switch (n) {
     case 8192: return launch_outer<W, 1>(P, products, inverse, s);
     case 16384: return launch_outer<W, 2>(P, products, inverse, s);
