@@ -30,7 +30,7 @@
 //
 // Measured against the 32x32-tile kernel on whole products, us per call (30-bit moduli):
 // n = 4096, 2048 products 364 -> 82 and 8 products 38.8 -> 14.2; n = 1024, 4095 products 55.5
-// -> 41.5; n = 8192, 512 products, 244 through two Karatsuba levels -> 77.  That kernel was bound
+// -> 41.5; n = 8192, 512 products, 244 through two Karatsuba levels -> 74.  That kernel was bound
 // by the power its matrix units draw.  Here the K loops take half of the time (left out, the
 // n = 4096 batch takes 42 us of 82): a step of sixteen MFMAs (256 cycles on each SIMD) reads
 // 9 KiB, the A runs five dwords a lane at 128 B a cycle, so four SIMDs' steps keep the LDS busy
@@ -59,7 +59,13 @@ struct PtGeom {
   static constexpr uint32_t kBPlane = (2 * kR - 1) * 16;      // rows -(R - 1) .. R - 1
   static constexpr uint32_t kColWords = 4 * kPtRow + (C > 1 ? 16 : 0);  // results of the c-th columns
   static constexpr uint32_t kResWords = C * kColWords;
-  template <int L> static constexpr uint32_t sub_bytes() { return (uint32_t)L * (kAPlane + kBPlane); }
+  // C = 2: the A planes of sub-product s start 4 (s % 4) bytes in.  A wave's store has the sixteen
+  // lanes of a row 16 C bytes apart; the shift puts its four rows, one sub-product each, on
+  // different banks (n = 8192, 512 products: 77.3 -> 74.1 us; level at C = 1, which goes without).  The B
+  // rows are read 16 bytes at a time and stay aligned.
+  static constexpr uint32_t kShift = C > 1 ? 4 : 0;
+  template <int L> static constexpr uint32_t b_at() { return (uint32_t)L * kAPlane + 4 * kShift; }
+  template <int L> static constexpr uint32_t sub_bytes() { return b_at<L>() + (uint32_t)L * kBPlane; }
 };
 // LDS: the planes of a batch (in the end the words two halves swap), then its results.
 template <typename W, int L, int C, int H>
@@ -291,7 +297,7 @@ __device__ __forceinline__ void pt_store(uint8_t* base, uint32_t plane, uint32_t
 }
 
 // Four points of the column group's four columns into the digit planes of sub-product
-// `sub` (this row's): the reversed ext of a, or the rows of b.  brow: the columns' index / 16;
+// `sub` (this row's; a: past its shift): the reversed ext of a, or the rows of b.  brow: the columns' index / 16;
 // cyclic: the sub-product is one of Z_q[y]/(y^M - 1), what wraps keeps its sign.
 template <int L, int C, bool IS_B, typename W, typename M>
 __device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const M& m, uint32_t wave, uint32_t brow,
@@ -306,7 +312,7 @@ __device__ __forceinline__ void pt_stage_planes(const W* v, uint8_t* sub, const 
 #pragma unroll
       for (int i = 0; i < 4; ++i) neg[i] = pos[i];
     }
-    uint8_t* rows = sub + L * G::kAPlane + 4 * wave;
+    uint8_t* rows = sub + G::template b_at<L>() + 4 * wave;
     pt_store<L>(rows, G::kBPlane, (brow + G::kR - 1) * 16, pos);
     if (brow > 0) pt_store<L>(rows, G::kBPlane, (brow - 1) * 16, neg);
   } else {
@@ -367,24 +373,26 @@ __device__ __forceinline__ uint64_t pt_recombine(const v4i_acc (&acc)[2 * L - 1]
   return pt_sub((uint64_t)(x1 >> 32), mulhi64(lo * pm.qinv, pm.m.q), pm.m.q);
 }
 
-// One 16x16 output tile (columns 16 tile + u) of a sub-product from its planes to its words:
+// One 16x16 output tile (columns 16 tile + u) of sub-product s of a batch from its planes to its words:
 // lane (u, g) leaves coefficients 16 (16 tile + u) + 4 g + e in row e of the results of columns
 // (16 tile + u) % C.  -c[M - 1] goes to slot 64 of the last columns' row 3, where column 0
 // finds y c.
 template <int L, int C, typename W, typename PM>
-__device__ __forceinline__ void pt_multiply(const uint8_t* sub, W* res, const PM& pm, uint32_t lane, uint32_t tile) {
+__device__ __forceinline__ void pt_multiply(const uint8_t* planes, W* results, uint32_t s, const PM& pm, uint32_t lane, uint32_t tile) {
   typedef PtGeom<C> G;
+  const uint8_t* ap = planes + s * G::template sub_bytes<L>() + G::kShift * (s & 3);
+  const uint8_t* bp = planes + s * G::template sub_bytes<L>() + G::template b_at<L>();
+  W* res = results + s * G::kResWords;
   const int zl = (int)(lane & 15), g = (int)(lane >> 4);
   const int S0 = G::kM - 1 - 16 * g - zl;
   const int B0 = (16 * (int)tile + zl + G::kR - 1 - g) * 16;
-  const uint8_t* bp = sub + L * G::kAPlane;
   v4i_acc acc[2 * L - 1];
 #pragma unroll
-  for (int s = 0; s < 2 * L - 1; ++s) acc[s] = v4i_acc{0, 0, 0, 0};
+  for (int d = 0; d < 2 * L - 1; ++d) acc[d] = v4i_acc{0, 0, 0, 0};
 #pragma unroll
   for (int st = 0; st < G::kM / 64; ++st) {
-    if constexpr (L <= 4) mfma16_step<L>(acc, sub, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
-    else pt_step_wide<L>(acc, sub, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
+    if constexpr (L <= 4) mfma16_step<L>(acc, ap, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
+    else pt_step_wide<L>(acc, ap, G::kAPlane, S0 - 64 * st, bp, G::kBPlane, B0 - 64 * st);
   }
   const uint32_t u = 16 * tile + zl;
   W* out = C == 1 ? res + lane : res + (u % C) * G::kColWords + 16 * g + u / C;
@@ -514,7 +522,7 @@ __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uin
     for (int h = 0; h < kPtBatch; h += 4) {
       uint8_t* sub = smem + (h + row) * kSub;
       if (H == 1 || half == 0)
-        pt_stage_planes<L, C, false>(v[0] + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c);
+        pt_stage_planes<L, C, false>(v[0] + ph * kPtBatch + h, sub + Geo::kShift * row, pm.m, w, C * yhigh + c);
       if (H == 1 || half == 1)
         pt_stage_planes<L, C, true>(v[OPS - 1] + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c);
     }
@@ -522,7 +530,7 @@ __device__ __forceinline__ void pt_group(const PtParams<W>& P, uint64_t grp, uin
     constexpr uint32_t kUnits = 2 / H;  // (sub-product, tile) units per wave
 #pragma unroll 1
     for (uint32_t i = kUnits * wave; i < kUnits * (wave + 1); ++i)
-      pt_multiply<L, C>(smem + i / C * kSub, results + i / C * Geo::kResWords, pm, lane, i % C);
+      pt_multiply<L, C>(smem, results, i / C, pm, lane, i % C);
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < kPtBatch; s += H) {
@@ -698,7 +706,7 @@ __device__ __forceinline__ void pt_cyclic_last(const uint32_t* e, const uint32_t
 // products put together, with a thread at words t + M m, all m < K: every word of global memory
 // is touched once, in whole rows; LDS hands the words over to the columns and back.  Bound as the
 // kernel above is.  Against the 32x32-tile kernel, four limbs, us: n = 2048, 1000 products 52.0 ->
-// 27.0, one 21.4 -> 13.7; n = 4096, 1024 products 188 -> 43; n = 8192, 512 products 392 -> 69.
+// 24.0, one 21.4 -> 13.7; n = 4096, 1024 products 188 -> 43; n = 8192, 512 products 392 -> 67.
 template <int L, int LK, int C>
 __global__ __launch_bounds__(512 * C) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void ptrans_cyclic_kernel(const PtParams<uint32_t> P) {
@@ -753,12 +761,12 @@ void ptrans_cyclic_kernel(const PtParams<uint32_t> P) {
     for (int h = 0; h < kPtBatch; h += 4) {
       uint8_t* sub = smem + (h + row) * kSub;
       const bool cyclic = last && h == kPtBatch - 4 && row == 1;
-      if (half == 0) pt_stage_planes<L, C, false>(v + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c, cyclic);
+      if (half == 0) pt_stage_planes<L, C, false>(v + ph * kPtBatch + h, sub + Geo::kShift * row, pm.m, w, C * yhigh + c, cyclic);
       else pt_stage_planes<L, C, true>(v + ph * kPtBatch + h, sub, pm.m, w, C * yhigh + c, cyclic);
     }
     __syncthreads();
     if (!last || wave / C < kPtBatch - 2)
-      pt_multiply<L, C>(smem + wave / C * kSub, results + wave / C * Geo::kResWords, pm, lane, wave % C);
+      pt_multiply<L, C>(smem, results, wave / C, pm, lane, wave % C);
     __syncthreads();
     const uint32_t q = pm.m.q;
 #pragma unroll
