@@ -24,7 +24,7 @@ sys.path.insert(0, ROOT)
 METRIC = "negacyclic polymuls/sec at n=4096 30-bit q (int8-MFMA vs plain int); % int8 peak"
 PEAK_INT8_TOPS = 5000.0      # MI355X dense int8 MFMA, published
 WORKLOAD_INDEX = 2
-KERNEL = "ptrans_kernel<4,4>"
+KERNEL = "ptrans_kernel<uint32_t, 4, 4, 1>"
 PT_POINTS, PT_DEGREE = 32, 256  # the headline route: 32 sub-products of degree 256 per product of degree 4096
 
 
@@ -198,8 +198,9 @@ def other_workloads(steps, warmup, pre_s=0.3):
     preheat(plan.execute, pre_s)
     ms = time_steps(plan.execute, steps, warmup)
     ops = sum(2 * 16 * g.n * g.n * g.count for g in w.groups)
-    out[w.name] = {"polymuls_per_s": w.products() / ms * 1e3, "ms_per_step": ms, "int8_tops": ops / ms / 1e9,
-                   "launch": "one persistent grouped kernel, hipGraph replay"}
+    out[w.name] = {"polymuls_per_s": w.products() / ms * 1e3, "ms_per_step": ms,
+                   "schoolbook_equivalent_tops": ops / ms / 1e9,
+                   "launch": "one persistent grouped kernel and the combine of n = 8192, hipGraph replay"}
     plan.close()
     w = inputs.make_workload(4)
     a = torch.from_numpy(w.a.view(np.int64)).to(dev)
@@ -208,15 +209,14 @@ def other_workloads(steps, warmup, pre_s=0.3):
     run = lambda: pm.polymul_negacyclic_u64(a, b, w.q, out=c)
     preheat(run, pre_s)
     ms = time_steps(run, max(2, steps // 20), 2)
-    ops = 2 * 64 * w.n * w.n * a.shape[0]
-    dk = pm.polymul_tune_get_karatsuba(w.n, a.shape[0], 8)
-    ws = torch.empty(max(16, pm.polymul_karatsuba_u64_workspace_size(w.n, a.shape[0], dk)), dtype=torch.uint8,
-                     device=dev)
+    # two operands of eight limbs through the transform: 32 points of degree 4096, each 32 of 256
+    ops = 2 * 64 * 32 * 32 * 256 ** 2 * a.shape[0]
+    ws = torch.empty(max(16, pm.polymul_karatsuba_u64_workspace_size(w.n, a.shape[0], 3)), dtype=torch.uint8, device=dev)
     ck = torch.empty_like(a)
-    msk = time_steps(lambda: pm.polymul_negacyclic_u64_karatsuba(a, b, w.q, dk, workspace=ws, out=ck),
+    msk = time_steps(lambda: pm.polymul_negacyclic_u64_karatsuba(a, b, w.q, 3, workspace=ws, out=ck),
                      max(2, steps // 20), 2)
     out[w.name] = {"polymuls_per_s": a.shape[0] / ms * 1e3, "ms_per_step": ms, "int8_tops": ops / ms / 1e9,
-                   "karatsuba_depth": dk, "karatsuba_polymuls_per_s": a.shape[0] / msk * 1e3,
+                   "karatsuba_depth": 3, "karatsuba_polymuls_per_s": a.shape[0] / msk * 1e3,
                    "karatsuba_ms_per_step": msk,
                    "karatsuba_bit_identical": bool(torch.equal(c, ck))}
     return out
@@ -238,7 +238,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--all", action="store_true", help="also time the other workloads (stderr)")
     ap.add_argument("--karatsuba-depth", type=int, default=0,
-                    help="levels of the Karatsuba route (0: the tuned depth; -1 skips the route)")
+                    help="levels of the Karatsuba route (0: the library's own choice; -1 skips the route)")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="first copy this many MiB device-to-device (reference for HBM byte counters)")
     args = ap.parse_args()
@@ -301,26 +301,31 @@ def main():
     ms_plain = time_steps(plain_run, max(1, min(args.steps, 5)), 1)
     plain_value = products / (ms_plain / 1e3)
 
+    # the clock a route finds is the one the route before it left: each gets a preheat of its own
+    side_s = min(args.preheat_s, 0.3)
     kara = None
     if args.karatsuba_depth >= 0:
-        d = args.karatsuba_depth or pm.polymul_tune_get_karatsuba(n, products, 4)
+        d = args.karatsuba_depth
         ws = torch.empty(max(16, pm.polymul_karatsuba_workspace_size(n, L, B, d)), dtype=torch.uint8, device=dev)
         ck = torch.empty_like(a)
-        ms_k = time_steps(lambda: pm.polymul_negacyclic_rns_karatsuba(a, b, w.qs, d, workspace=ws, out=ck),
-                          args.steps, args.warmup)
+        run = lambda: pm.polymul_negacyclic_rns_karatsuba(a, b, w.qs, d, workspace=ws, out=ck)
+        preheat(run, side_s)
+        ms_k = time_steps(run, args.steps, args.warmup)
         pm.polymul_negacyclic_rns(a, b, w.qs, out=c)
         torch.cuda.synchronize()
         kara = {"depth": d, "value": products / (ms_k / 1e3), "unit": "polymuls/s", "ms_per_step": ms_k,
                 "speedup_vs_direct": ms / ms_k, "bit_identical_to_direct": bool(torch.equal(ck, c)),
                 "kernels": ("split, matrix kernel on 3^d sub-products of degree n/2^d, combine" if d else
-                            "direct route (the tuned depth is 0)"),
+                            f"the library's own choice, for odd moduli the transform ({KERNEL})"),
                 "schoolbook_equivalent_tops": 2 * 16 * n * n * products / ms_k / 1e9}
         del ws, ck
 
-    # one b per channel shared by all 256 pairs (same shapes and work, b staged once per chunk)
+    # one b per channel shared by all 256 pairs (same shapes and work)
     bs = b[0].contiguous()
     cs = torch.empty_like(a)
-    ms_s = time_steps(lambda: pm.polymul_negacyclic_rns_shared(a, bs, w.qs, out=cs), args.steps, args.warmup)
+    run = lambda: pm.polymul_negacyclic_rns_shared(a, bs, w.qs, out=cs)
+    preheat(run, side_s)
+    ms_s = time_steps(run, args.steps, args.warmup)
     shared = {"value": products / (ms_s / 1e3), "unit": "polymuls/s", "ms_per_step": ms_s,
               "speedup_vs_direct": ms / ms_s, "b": "pair 0's b for every pair, one per channel",
               "kernel": KERNEL}
@@ -328,7 +333,9 @@ def main():
 
     # the paper's own coefficient method: 8-bit co-prime moduli and CRT (9 residue channels here)
     cc = torch.empty_like(a)
-    ms_c = time_steps(lambda: pm.polymul_negacyclic_rns_crt(a, b, w.qs, out=cc), args.steps, args.warmup)
+    run = lambda: pm.polymul_negacyclic_rns_crt(a, b, w.qs, out=cc)
+    preheat(run, side_s)
+    ms_c = time_steps(run, args.steps, args.warmup)
     chans = len(pm.polymul_crt_moduli(n, max(w.qs)))
     # LDS bytes read per lane and K-step of one channel: two A runs (five dwords each) and two
     # B runs (16 bytes each) feed the four MFMAs of a product's 2 x 2 tiles

@@ -152,10 +152,11 @@ polymul_status polymul_plan_destroy(polymul_plan* plan);
  * Arguments, layout and errors as polymul_negacyclic / polymul_negacyclic_rns;
  * n <= 4096 (the residue planes of both operands live in LDS), else
  * POLYMUL_EUNSUPPORTED.  Speed: at n = 4096 (one product's four output tiles share
- * their operand fragments in 2 x 2) this route runs 1.1x the limb route; below, each
- * product is a single output tile, every MFMA reads its own fragments and the
- * channels' planes leave one workgroup per CU, and the limb route is much faster
- * (n = 1024: about 7x, n = 512: about 14x).
+ * their operand fragments in 2 x 2) this route runs 1.1x the limb products on tiles of
+ * the whole product (even moduli) and a quarter of the polynomial transform's rate;
+ * below, each product is a single output tile, every MFMA reads its own fragments
+ * and the channels' planes leave one workgroup per CU, and the limb route is much
+ * faster (on tiles n = 1024: about 7x, n = 512: about 14x).
  */
 polymul_status polymul_negacyclic_crt(const uint32_t* a, const uint32_t* b, uint32_t* c,
                                       uint64_t n, uint32_t q, uint64_t batch, hipStream_t stream);
@@ -229,7 +230,8 @@ polymul_status polymul_karatsuba_workspace_size(uint64_t n, uint32_t L, uint64_t
  * polymul_negacyclic_u64): the sub-products run on the K-streaming kernel,
  * their K range cut into up to four runs (POLYMUL_TUNE_U64_KARATSUBA_RUNS) when
  * that fills the GPU's rounds of workgroups better.  depth 0 takes the tuned
- * choice for (n, batch) as above, the direct polymul_negacyclic_u64 included.  Workspace rules and errors as above, sized by
+ * choice for (n, batch) as above, the direct polymul_negacyclic_u64 included.
+ * Workspace rules and errors as above, sized by
  * polymul_karatsuba_u64_workspace_size (room for the runs included).
  */
 polymul_status polymul_karatsuba_u64_workspace_size(uint64_t n, uint64_t batch, uint32_t depth,
@@ -271,11 +273,12 @@ polymul_status polymul_negacyclic_rns_karatsuba_noalloc(const uint32_t* a, const
  * cut into (n = t * r): n itself when n <= 32, otherwise a power of two in
  * [32, min(n, 128)] (32x32 output tiles, v_mfma_i32_32x32x32_i8), or 16 for
  * 64 <= n <= 512 (16x16 output tiles, v_mfma_i32_16x16x64_i8, the built-in
- * choice there).  t = 0 restores the built-in choice, which for n = 1024..4096 and
- * odd moduli is the polynomial transform instead of tiles of the whole product.  The table is
- * process-wide; the autotuner (paper_2307_06554_amd/tune.py) times the
- * candidates on the GPU and calls polymul_tune_set with the winners.  Takes
- * effect for launches and plans created afterwards.  No HIP call is made.
+ * choice there).  t = 0 restores the built-in choice, which for n = 1024..8192 and
+ * odd moduli is the polynomial transform instead of tiles of the whole product (both
+ * rings; not at every limb count when n = 1024).  The table is process-wide;
+ * the autotuner (paper_2307_06554_amd/tune.py) times the candidates on the GPU
+ * and calls polymul_tune_set with the winners.  Takes effect for launches and
+ * plans created afterwards.  No HIP call is made.
  * EINVAL: bad n, L or t; EUNSUPPORTED: the tile does not fit in LDS.
  */
 polymul_status polymul_tune_set(uint64_t n, uint32_t L, uint32_t t);

@@ -7,8 +7,9 @@ experiments are automated and their winners loaded into the library:
   - the Toeplitz tile side t of the resident 32-bit path per degree bound n
     (16: the 16x16-tile kernel; 32, 64, 128: 32x32 tiles; 0: the library's own
     choice, which for the degrees it takes is the polynomial transform), polymul_tune_set;
-  - the Karatsuba depth per degree bound and batch (the direct route included),
-    for 32-bit RNS products and for 64-bit words, polymul_tune_set_karatsuba;
+  - the Karatsuba depth per degree bound and batch (the built-in choice, which is the
+    transform where it takes the modulus, and the direct route included), for 32-bit RNS
+    products and for 64-bit words, polymul_tune_set_karatsuba;
   - the K-run cap of the 64-bit Karatsuba route and the two scheduling knobs of
     grouped plans (split threshold, weight of streamed blocks),
     polymul_tune_param_set.
@@ -128,60 +129,63 @@ def tune_tiles(ns, Ls, work, log):
     return entries
 
 
+BUILTIN = binding.KARATSUBA_BUILTIN
+
+
+def _depth_name(d):
+    return "built-in" if d == BUILTIN else str(d)
+
+
 def tune_karatsuba(shapes, log):
-    """32-bit RNS products: (n, channels, batch) shapes; depth 0 = the direct route."""
+    """32-bit RNS products: (n, channels, batch) shapes.  Each choice is timed as depth 0 of a caller
+    meets it: nothing tuned (the polynomial transform, where it takes the moduli), the direct
+    route (0), or 1..3 levels."""
     import torch
     entries = []
     for n, L, batch in shapes:
         qs = [Q30] * L
         a, b = _rand((batch, L, n), Q30, n + 7), _rand((batch, L, n), Q30, n + 8)
         c = a.clone()
-        timings = {0: time_us(lambda: binding.polymul_negacyclic_rns(a, b, qs, out=c))}
-        for d in (1, 2, 3):
-            if (n >> d) < 4:
-                continue
-            ws = torch.empty(max(16, binding.polymul_karatsuba_workspace_size(n, L, batch, d)), dtype=torch.uint8,
+        timings = {}
+        for d in (BUILTIN, 0, 1, 2, 3):
+            binding.polymul_tune_set_karatsuba(n, batch * L, 4, d)
+            ws = torch.empty(max(16, binding.polymul_karatsuba_workspace_size(n, L, batch, 0)), dtype=torch.uint8,
                              device="cuda")
-            timings[d] = time_us(lambda: binding.polymul_negacyclic_rns_karatsuba(a, b, qs, d, workspace=ws, out=c))
+            timings[d] = time_us(lambda: binding.polymul_negacyclic_rns_karatsuba(a, b, qs, 0, workspace=ws, out=c))
             del ws
-        binding.polymul_tune_set_karatsuba(n, batch * L, 4, binding.KARATSUBA_BUILTIN)
-        best = pick(timings, binding.polymul_tune_get_karatsuba(n, batch * L, 4))
+        best = pick(timings, BUILTIN)
         log(f"karatsuba n={n:6d} products={batch * L:6d} " +
-            " ".join(f"d={d}:{us:8.1f}us" for d, us in timings.items()) + f"  -> depth {best}")
+            " ".join(f"d={_depth_name(d)}:{us:8.1f}us" for d, us in timings.items()) + f"  -> depth {_depth_name(best)}")
         entries.append({"n": n, "products": batch * L, "depth": best,
-                        "timings_us": {str(k): v for k, v in timings.items()}})
+                        "timings_us": {_depth_name(k): v for k, v in timings.items()}})
         binding.polymul_tune_set_karatsuba(n, batch * L, 4, best)
     return entries
 
 
 def tune_karatsuba64(shapes, log):
-    """64-bit words (Goldilocks): depth 0..3 and the K-run cap of the streamed sub-products."""
+    """64-bit words (Goldilocks): the same choices, and the K-run cap of the streamed sub-products."""
     import torch
     entries = []
     best_runs = 4
     for n, batch in shapes:
         a, b = _rand((batch, n), GOLDILOCKS, n + 9, 64), _rand((batch, n), GOLDILOCKS, n + 10, 64)
         c = a.clone()
-        timings = {"0": time_us(lambda: binding.polymul_negacyclic_u64(a, b, GOLDILOCKS, out=c), reps=4,
-                                trials=2)}
-        for d in (1, 2, 3):
-            ws = torch.empty(max(16, binding.polymul_karatsuba_u64_workspace_size(n, batch, d)), dtype=torch.uint8,
+        timings = {}
+        for d, runs in [(BUILTIN, 4), (0, 4)] + [(d, runs) for d in (1, 2, 3) for runs in (1, 2, 4)]:
+            binding.polymul_tune_set_karatsuba(n, batch, 8, d)
+            binding.polymul_tune_param_set("u64_karatsuba_runs", runs)
+            ws = torch.empty(max(16, binding.polymul_karatsuba_u64_workspace_size(n, batch, 0)), dtype=torch.uint8,
                              device="cuda")
-            for runs in (1, 2, 4):
-                binding.polymul_tune_param_set("u64_karatsuba_runs", runs)
-                timings[f"{d}/{runs}"] = time_us(
-                    lambda: binding.polymul_negacyclic_u64_karatsuba(a, b, GOLDILOCKS, d, workspace=ws, out=c),
-                    reps=4, trials=2)
+            timings[d, runs] = time_us(
+                lambda: binding.polymul_negacyclic_u64_karatsuba(a, b, GOLDILOCKS, 0, workspace=ws, out=c), reps=4, trials=2)
             del ws
-        binding.polymul_tune_param_set("u64_karatsuba_runs", 4)
-        binding.polymul_tune_set_karatsuba(n, batch, 8, binding.KARATSUBA_BUILTIN)
-        d0 = binding.polymul_tune_get_karatsuba(n, batch, 8)
-        key = pick(timings, "0" if d0 == 0 else f"{d0}/4")
-        depth, runs = (0, 4) if key == "0" else (int(key.split("/")[0]), int(key.split("/")[1]))
-        log(f"karatsuba64 n={n:6d} products={batch:4d} " +
-            " ".join(f"{k}:{us:8.1f}us" for k, us in timings.items()) + f"  -> depth {depth}, runs {runs}")
-        entries.append({"n": n, "products": batch, "depth": depth, "runs": runs, "timings_us": timings})
+        depth, runs = pick(timings, (BUILTIN, 4))
+        binding.polymul_tune_param_set("u64_karatsuba_runs", runs)
         binding.polymul_tune_set_karatsuba(n, batch, 8, depth)
+        named = {f"{_depth_name(d)}/{r}": us for (d, r), us in timings.items()}
+        log(f"karatsuba64 n={n:6d} products={batch:4d} " + " ".join(f"{k}:{us:8.1f}us" for k, us in named.items()) +
+            f"  -> depth {_depth_name(depth)}, runs {runs}")
+        entries.append({"n": n, "products": batch, "depth": depth, "runs": runs, "timings_us": named})
         best_runs = runs
     return entries, best_runs
 
