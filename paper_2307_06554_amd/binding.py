@@ -185,12 +185,13 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
     """call(a, b, c pointers, rows, workspace pointer, its bytes, stream) over the `rows` rows of
     a, b and c, in chunks with a workspace of size(rows of the chunk) bytes; False where nothing
     was launched.  The workspace is torch memory of the current stream, so only calls on that
-    stream, on the tensors' own device, take it."""
+    stream, on the tensors' own device, take it; and not while the stream is being captured, when
+    torch cannot be relied on to keep that memory for the graph's replays."""
     import torch
     if not a.is_cuda or a.device.index != torch.cuda.current_device():
         return False
     raw = _stream(stream)
-    if stream is not None and raw.value != _stream(None).value:
+    if (stream is not None and raw.value != _stream(None).value) or torch.cuda.is_current_stream_capturing():
         return False
     chunk = max(1, min(rows, _WS_BYTES * rows // max(1, size(rows))))
     need = max(16, size(chunk), size(rows % chunk) if rows % chunk else 0)

@@ -154,6 +154,29 @@ def test_direct_call_in_chunks_and_on_another_stream(monkeypatch):
     check(to_host(got, np.uint64), want, "current stream")
 
 
+def test_captured_call_takes_no_workspace(monkeypatch):
+    import torch
+    from paper_2307_06554_amd import binding
+    rng = np.random.default_rng(10)
+    a, b = edge_operands64(rng, 2, 8192, GOLDILOCKS)
+    want = oracle.negacyclic(a, b, GOLDILOCKS)
+    da, db = to_dev(a), to_dev(b)
+    c = torch.empty_like(da)
+    pm.polymul_negacyclic_u64(da, db, GOLDILOCKS, out=c)
+    sizes = []
+    size = binding.polymul_karatsuba_u64_workspace_size
+    monkeypatch.setattr(binding, "polymul_karatsuba_u64_workspace_size", lambda *v: sizes.append(v) or size(*v))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pm.polymul_negacyclic_u64(da, db, GOLDILOCKS, out=c)
+    assert not sizes
+    for _ in range(3):
+        c.fill_(-1)
+        graph.replay()
+        check(to_host(c, np.uint64), want, "replay")
+        check(to_host(pm.polymul_negacyclic_u64(da, db, GOLDILOCKS), np.uint64), want, "eager between replays")
+
+
 def test_plan_groups():
     """Plan items on the transform: full and ragged items of every degree, two groups of n = 8192 (their
     sub-products share the plan's buffer), moduli that stay on the tiles beside them, replays."""
