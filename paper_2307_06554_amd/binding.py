@@ -193,13 +193,16 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
     raw = _stream(stream)
     if (stream is not None and raw.value != _stream(None).value) or torch.cuda.is_current_stream_capturing():
         return False
+    pa, pb, pc = _words(a, nbytes, "a").value, _words(b, nbytes, "b").value, _words(c, nbytes, "out").value
+    total = a.numel() * nbytes
+    if abs(pc - pa) < total or abs(pc - pb) < total:
+        return False  # refused by the direct call; a chunk might not see the overlap
     chunk = max(1, min(rows, _WS_BYTES * rows // max(1, size(rows))))
     need = max(16, size(chunk), size(rows % chunk) if rows % chunk else 0)
     try:
         ws = torch.empty(need, dtype=torch.uint8, device=a.device)
     except torch.cuda.OutOfMemoryError:
         return False
-    pa, pb, pc = _words(a, nbytes, "a").value, _words(b, nbytes, "b").value, _words(c, nbytes, "out").value
     step = a.numel() // rows * nbytes
     for r in range(0, rows, chunk):
         _check(call(pa + r * step, pb + r * step, pc + r * step, min(chunk, rows - r), ws.data_ptr(), need, raw), name)

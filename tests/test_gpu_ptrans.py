@@ -154,6 +154,17 @@ def test_direct_call_in_chunks_and_on_another_stream(monkeypatch):
     check(to_host(got, np.uint64), want, "current stream")
 
 
+def test_overlapping_output_is_refused_whatever_the_chunks(monkeypatch):
+    import torch
+    from paper_2307_06554_amd import binding
+    buf = torch.zeros((8, 8192), dtype=torch.int64, device="cuda")
+    b = torch.zeros((5, 8192), dtype=torch.int64, device="cuda")
+    monkeypatch.setattr(binding, "_WS_BYTES", pm.polymul_karatsuba_u64_workspace_size(8192, 1, 0))  # rows one by one
+    for x, y in ((buf[:5], b), (b, buf[:5])):
+        with pytest.raises(pm.PolymulError):
+            pm.polymul_negacyclic_u64(x, y, GOLDILOCKS, out=buf[3:])
+
+
 def test_captured_call_takes_no_workspace(monkeypatch):
     import torch
     from paper_2307_06554_amd import binding
