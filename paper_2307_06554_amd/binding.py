@@ -225,7 +225,7 @@ def polymul_negacyclic(a, b, q, out=None, stream=None):
     """c = a*b in Z_q[x]/(x^n+1) for 32-bit words [..., n], q < 2^32 (int8-MFMA path)."""
     n, batch = _pair(a, b)
     c = _result(out, a, 4)
-    if n >= _WS_DEGREE[4] and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
+    if n > 8192 and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
         return c
     st = load_library().polymul_negacyclic(_words(a, 4, "a"), _words(b, 4, "b"), _words(c, 4, "out"),
                                           n, int(q), batch, _stream(stream))
@@ -284,7 +284,7 @@ def polymul_negacyclic_rns(a, b, qs, out=None, stream=None):
     """RNS form: a, b are 32-bit words [batch, L, n]; channel l is taken mod qs[l]."""
     batch, L, n = _rns_shape(a, b, qs)
     c = _result(out, a, 4)
-    if n >= _WS_DEGREE[4] and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
+    if n > 8192 and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
                                                   stream):
         return c
     qarr = (ctypes.c_uint32 * L)(*[int(x) for x in qs])
