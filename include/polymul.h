@@ -246,6 +246,30 @@ polymul_status polymul_negacyclic_rns_karatsuba(const uint32_t* a, const uint32_
                                                 uint64_t workspace_bytes, hipStream_t stream);
 
 /*
+ * polymul_negacyclic_rns and polymul_negacyclic_u64 with a workspace that the caller
+ * owns.  Above n = 8192 (64-bit words: 4096) products under moduli that the polynomial
+ * transform takes (odd; at most 0x7F7F7F7F for 32-bit words) then run through an outer
+ * transform whose points the workspace holds, 4 n words per product; everywhere else
+ * the calls are the ones named above and the workspace is not used.  The Karatsuba
+ * table has no part in them.
+ *   polymul_workspace_size: bytes for `products` products (batch * L, or batch) of
+ *                degree bound n in words of elem_bytes (4 or 8); 0 where none is used.
+ *                Host only, no HIP call.  EINVAL: bad n, elem_bytes, null pointer or a
+ *                size beyond 2^62.
+ *   L:           at most 16 with a workspace in use (else it is not used).
+ *   workspace:   device, 16-byte aligned, not overlapping a, b or c; its contents on
+ *                entry do not matter.  EINVAL: missing, misaligned or too small;
+ *                EALIAS: it overlaps an array.  Other errors as the calls named above.
+ */
+polymul_status polymul_workspace_size(uint64_t n, uint64_t products, uint32_t elem_bytes, uint64_t* bytes);
+polymul_status polymul_negacyclic_rns_workspace(const uint32_t* a, const uint32_t* b, uint32_t* c, uint64_t n,
+                                                const uint32_t* q, uint32_t L, uint64_t batch, void* workspace,
+                                                uint64_t workspace_bytes, hipStream_t stream);
+polymul_status polymul_negacyclic_u64_workspace(const uint64_t* a, const uint64_t* b, uint64_t* c, uint64_t n,
+                                                uint64_t q, uint64_t batch, void* workspace,
+                                                uint64_t workspace_bytes, hipStream_t stream);
+
+/*
  * polymul_negacyclic_rns_karatsuba for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the workspace is not an argument but a buffer of

@@ -43,6 +43,9 @@ _SIGNATURES = {
     "polymul_karatsuba_workspace_size": (ctypes.c_int, [_u64, _u32, _u64, _u32, ctypes.POINTER(_u64)]),
     "polymul_negacyclic_rns_karatsuba": (ctypes.c_int, [_vp, _vp, _vp, _u64, _vp, _u32, _u64, _u32, _vp, _u64,
                                                         _vp]),
+    "polymul_workspace_size": (ctypes.c_int, [_u64, _u64, _u32, ctypes.POINTER(_u64)]),
+    "polymul_negacyclic_rns_workspace": (ctypes.c_int, [_vp, _vp, _vp, _u64, _vp, _u32, _u64, _vp, _u64, _vp]),
+    "polymul_negacyclic_u64_workspace": (ctypes.c_int, [_vp, _vp, _vp, _u64, _u64, _u64, _vp, _u64, _vp]),
     "polymul_tune_get": (ctypes.c_int, [_u64, _u32, ctypes.POINTER(_u32)]),
     "polymul_negacyclic_rns_karatsuba_noalloc": (ctypes.c_int, [_vp, _vp, _vp, _u64, _vp, _u32, _u64, _u32, _vp]),
     "polymul_tune_param_set": (ctypes.c_int, [_u32, _u64]),
@@ -170,10 +173,10 @@ def _rns_shape(a, b, qs):
 
 # Products of degree _WS_DEGREE[bytes per word] and above run fastest through a workspace (an
 # outer polynomial transform around the one of degree 4096; odd moduli).  The direct calls take it
-# from torch's caching allocator, about _WS_BYTES at a time, and go without where that would
+# from torch's caching allocator, at most _WS_BYTES at a time, and go without where that would
 # not be safe or there is no room.
 _WS_DEGREE = {4: 16384, 8: 8192}
-_WS_BYTES = 512 << 20
+_WS_BYTES = 128 << 20
 _WS_MAX_Q32 = 0x7F7F7F7F
 
 
@@ -181,9 +184,9 @@ def _large(n, rows, nbytes):
     return rows > 0 and _WS_DEGREE[nbytes] <= n <= 65536 and n & (n - 1) == 0
 
 
-def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
+def _through_workspace(name, nbytes, a, b, c, n, rows, stream, call):
     """call(a, b, c pointers, rows, workspace pointer, its bytes, stream) over the `rows` rows of
-    a, b and c, in chunks with a workspace of size(rows of the chunk) bytes; False where nothing
+    a, b and c, as many at a time as _WS_BYTES of workspace hold; False where nothing
     was launched.  The workspace is torch memory of the current stream, so only calls on that
     stream, on the tensors' own device, take it; and not while the stream is being captured, when
     torch cannot be relied on to keep that memory for the graph's replays."""
@@ -197,15 +200,16 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, size, call):
     total = a.numel() * nbytes
     if abs(pc - pa) < total or abs(pc - pb) < total:
         return False  # refused by the direct call; a chunk might not see the overlap
-    chunk = max(1, min(rows, _WS_BYTES * rows // max(1, size(rows))))
-    need = max(16, size(chunk), size(rows % chunk) if rows % chunk else 0)
+    row = total // rows
+    per_row = polymul_workspace_size(n, row // (n * nbytes), nbytes)
+    chunk = max(1, min(rows, _WS_BYTES // per_row))
+    need = chunk * per_row
     try:
         ws = torch.empty(need, dtype=torch.uint8, device=a.device)
     except torch.cuda.OutOfMemoryError:
         return False
-    step = a.numel() // rows * nbytes
     for r in range(0, rows, chunk):
-        _check(call(pa + r * step, pb + r * step, pc + r * step, min(chunk, rows - r), ws.data_ptr(), need, raw), name)
+        _check(call(pa + r * row, pb + r * row, pc + r * row, min(chunk, rows - r), ws.data_ptr(), need, raw), name)
     return True
 
 
@@ -216,9 +220,8 @@ def _rns_through_workspace(name, a, b, c, n, qs, batch, stream):
     lib = load_library()
     qarr = (ctypes.c_uint32 * L)(*qs)
     return _through_workspace(
-        name, 4, a, b, c, n, batch, stream, lambda rows: polymul_karatsuba_workspace_size(n, L, rows, 0),
-        lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_rns_karatsuba(
-            pa, pb, pc, n, ctypes.cast(qarr, ctypes.c_void_p), L, rows, 0, ws, size, st))
+        name, 4, a, b, c, n, batch, stream, lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_rns_workspace(
+            pa, pb, pc, n, ctypes.cast(qarr, ctypes.c_void_p), L, rows, ws, size, st))
 
 
 def polymul_negacyclic(a, b, q, out=None, stream=None):
@@ -251,9 +254,8 @@ def polymul_negacyclic_u64(a, b, q, out=None, stream=None):
         lib = load_library()
         if _through_workspace(
                 "polymul_negacyclic_u64", 8, a, b, c, n, batch, stream,
-                lambda rows: polymul_karatsuba_u64_workspace_size(n, rows, 0),
-                lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_u64_karatsuba(
-                    pa, pb, pc, n, int(q), rows, 0, ws, size, st)):
+                lambda pa, pb, pc, rows, ws, size, st: lib.polymul_negacyclic_u64_workspace(
+                    pa, pb, pc, n, int(q), rows, ws, size, st)):
             return c
     st = load_library().polymul_negacyclic_u64(_words(a, 8, "a"), _words(b, 8, "b"), _words(c, 8, "out"),
                                               n, int(q), batch, _stream(stream))
@@ -354,6 +356,14 @@ def polymul_negacyclic_rns_shared(a, b, qs, out=None, stream=None):
                                                      _stream(stream))
     _check(st, "polymul_negacyclic_rns_shared")
     return c
+
+
+def polymul_workspace_size(n, products, elem_bytes):
+    """Bytes of device workspace that `products` direct products of degree bound n run fastest with."""
+    out = ctypes.c_uint64()
+    _check(load_library().polymul_workspace_size(int(n), int(products), int(elem_bytes), ctypes.byref(out)),
+           "polymul_workspace_size")
+    return out.value
 
 
 def polymul_karatsuba_workspace_size(n, L, batch, depth):

@@ -69,6 +69,14 @@ polymul_status check_shared(const void* a, const void* b, const void* c, uint64_
   return POLYMUL_OK;
 }
 
+// A caller's workspace: there, aligned, large enough and apart from the arrays of `bytes` bytes.
+polymul_status check_workspace(const void* ws, uint64_t ws_bytes, uint64_t need, const void* a, const void* b,
+                               const void* c, uint64_t bytes) {
+  if (!ws || ((uintptr_t)ws & 15) || ws_bytes < need) return POLYMUL_EINVAL;
+  if (overlaps(ws, need, a, bytes) || overlaps(ws, need, b, bytes) || overlaps(ws, need, c, bytes)) return POLYMUL_EALIAS;
+  return POLYMUL_OK;
+}
+
 // POLYMUL_LOG=1 in the environment prints failing HIP calls to stderr.
 bool log_enabled() {
   static const bool on = [] {
@@ -776,6 +784,10 @@ polymul_status launch_outer_n(const PtOuter<W>& P, uint64_t n, uint64_t products
     default: return launch_outer<W, 4>(P, products, inverse, s);
   }
 }
+
+// Words of its workspace, and whether degree n runs through it where there is one.
+uint64_t outer_words(uint64_t n, uint64_t products) { return 4 * n * products; }
+bool outer_degree(uint64_t n, uint32_t elem) { return n > (elem == 8 ? kPtOuterM : 2 * kPtOuterM); }
 
 template <typename W>
 void fill_outer(PtOuter<W>& O, const W* a, const W* b, W* c, uint64_t n, uint64_t products, uint32_t L, void* ws) {
@@ -1565,6 +1577,46 @@ polymul_status polymul_negacyclic_u64_shared(const uint64_t* a, const uint64_t* 
   return run_u64(a, b, c, (uint32_t)n, q, batch, stream, true);
 }
 
+polymul_status polymul_workspace_size(uint64_t n, uint64_t products, uint32_t elem_bytes, uint64_t* bytes) {
+  if (!bytes || !is_pow2(n) || n > 65536 || (elem_bytes != 4 && elem_bytes != 8)) return POLYMUL_EINVAL;
+  if (products >> 40) return POLYMUL_EINVAL;
+  *bytes = outer_degree(n, elem_bytes) ? outer_words(n, products) * elem_bytes : 0;
+  return POLYMUL_OK;
+}
+
+polymul_status polymul_negacyclic_rns_workspace(const uint32_t* a, const uint32_t* b, uint32_t* c, uint64_t n,
+                                                const uint32_t* q, uint32_t L, uint64_t batch, void* workspace,
+                                                uint64_t workspace_bytes, hipStream_t stream) {
+  if (L == 0 || !q) return POLYMUL_EINVAL;
+  bool outer = outer_degree(n, 4) && L <= (uint32_t)kMaxQ;
+  for (uint32_t l = 0; l < L; ++l) {
+    if (q[l] < 2) return POLYMUL_EINVAL;
+    outer = outer && ptrans_modulus(q[l]);
+  }
+  if (!outer) return polymul_negacyclic_rns(a, b, c, n, q, L, batch, stream);
+  uint64_t bytes;
+  polymul_status st = check_arrays(a, b, c, n, batch, L, 4, &bytes);
+  if (st != POLYMUL_OK || batch == 0) return st;
+  st = check_workspace(workspace, workspace_bytes, outer_words(n, batch * L) * 4, a, b, c, bytes);
+  return st == POLYMUL_OK ? run_outer32(a, b, c, n, q, L, batch, workspace, stream) : st;
+}
+
+polymul_status polymul_negacyclic_u64_workspace(const uint64_t* a, const uint64_t* b, uint64_t* c, uint64_t n,
+                                                uint64_t q, uint64_t batch, void* workspace,
+                                                uint64_t workspace_bytes, hipStream_t stream) {
+  if (q < 2) return POLYMUL_EINVAL;
+  uint64_t bytes;
+  polymul_status st = check_arrays(a, b, c, n, batch, 1, 8, &bytes);
+  if (st != POLYMUL_OK || batch == 0) return st;
+  const uint32_t points = (uint32_t)(2 * n / kPtOuterM);
+  PtParams<uint64_t> P;
+  int L;
+  if (!outer_degree(n, 8) || !fill_ptrans64(P, a, b, c, kPtOuterM, q, batch * points, false, points, &L))
+    return run_u64(a, b, c, (uint32_t)n, q, batch, stream, false);
+  st = check_workspace(workspace, workspace_bytes, outer_words(n, batch) * 8, a, b, c, bytes);
+  return st == POLYMUL_OK ? run_outer64(a, b, c, n, batch, P, L, workspace, stream) : st;
+}
+
 polymul_status polymul_karatsuba_workspace_size(uint64_t n, uint32_t L, uint64_t batch, uint32_t depth,
                                                 uint64_t* bytes) {
   if (L < 1 || L > 16) return POLYMUL_EINVAL;
@@ -1590,9 +1642,8 @@ polymul_status polymul_negacyclic_u64_karatsuba(const uint64_t* a, const uint64_
   uint64_t bytes;
   st = check_arrays(a, b, c, n, batch, 1, 8, &bytes);
   if (st != POLYMUL_OK || batch == 0) return st;
-  if (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need) return POLYMUL_EINVAL;
-  if (overlaps(workspace, need, a, bytes) || overlaps(workspace, need, b, bytes) || overlaps(workspace, need, c, bytes))
-    return POLYMUL_EALIAS;
+  st = check_workspace(workspace, workspace_bytes, need, a, b, c, bytes);
+  if (st != POLYMUL_OK) return st;
   if (choose && n >= 1024) {  // the transform, where it takes the modulus
     const uint32_t points = n > kPtOuterM ? (uint32_t)(2 * n / kPtOuterM) : 1;
     PtParams<uint64_t> P;
@@ -1660,9 +1711,8 @@ polymul_status polymul_negacyclic_rns_karatsuba(const uint32_t* a, const uint32_
   uint64_t need, bytes;
   polymul_status st = check_rns_karatsuba(a, b, c, n, q, L, batch, depth, &need, &bytes);
   if (st != POLYMUL_OK || batch == 0) return st;
-  if (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need) return POLYMUL_EINVAL;
-  if (overlaps(workspace, need, a, bytes) || overlaps(workspace, need, b, bytes) || overlaps(workspace, need, c, bytes))
-    return POLYMUL_EALIAS;
+  st = check_workspace(workspace, workspace_bytes, need, a, b, c, bytes);
+  if (st != POLYMUL_OK) return st;
   return run_rns_karatsuba(a, b, c, n, q, L, batch, depth, choose, workspace, stream);
 }
 

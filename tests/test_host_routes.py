@@ -1,0 +1,106 @@
+"""What the library's host code launches and allocates, on a HIP runtime without a GPU
+(host/fake_hip.cpp): nothing is computed here."""
+import json
+import os
+import re
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+import paper_2307_06554_amd as pm
+from paper_2307_06554_amd import binding
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+
+# made-up device addresses, far enough apart for the largest calls here
+A, B, C, W = (k << 44 for k in (1, 2, 3, 4))
+Q30, EVEN = 1068236801, 1 << 20
+GOLDILOCKS = (1 << 64) - (1 << 32) + 1
+
+
+@pytest.fixture(scope="module")
+def drive(tmp_path_factory):
+    fake = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", os.path.join(HERE, "host", "fake_hip.cpp"), "-o", fake],
+                   check=True, capture_output=True, text=True)
+
+    def run(calls):
+        res = subprocess.run([sys.executable, os.path.join(HERE, "host_routes.py"), fake, pm.lib_path(), binding.__file__,
+                              json.dumps(calls)], capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0, res.stdout + res.stderr
+        return [json.loads(line) for line in res.stdout.splitlines()]
+
+    return run
+
+
+def kernels(result):
+    """Names of the launched kernels, without namespace and template arguments."""
+    return [re.sub(r"^_ZN?(2pm|12_GLOBAL__N_1)?\d*", "", launch[0]) for launch in result["launches"]]
+
+
+def call(fn, *args, **more):
+    return dict(fn=fn, args=list(args), **more)
+
+
+# ------------------------------------------------------------ direct calls with a workspace
+def outer_words_used(result, word):
+    """Words from the start of the workspace to the end of b's points, as the outer launch has them:
+    a, b, c, a's points, b's points."""
+    a, b, c, sa, sb = (int(v) for v in result["launches"][0][5:10])
+    return sa, (sb - sa) // word * 2
+
+
+@pytest.mark.parametrize("n,products", [(16384, 48), (32768, 5), (65536, 16)])
+def test_workspace_is_what_the_transform_uses(drive, n, products):
+    size = binding.polymul_workspace_size(n, products, 4)
+    got = drive([call("polymul_negacyclic_rns_workspace", A, B, C, n, {"u32": [Q30]}, 1, products, W, size, None)])[0]
+    assert got["status"] == 0
+    assert [k for k in kernels(got) if "outer" in k] and "pt_outer_forward" in got["launches"][0][0]
+    assert outer_words_used(got, 4) == (W, size // 4)
+    size = binding.polymul_workspace_size(n, products, 8)
+    got = drive([call("polymul_negacyclic_u64_workspace", A, B, C, n, GOLDILOCKS, products, W, size, None)])[0]
+    assert got["status"] == 0 and outer_words_used(got, 8) == (W, size // 8)
+    assert size == 4 * n * products * 8
+
+
+def test_karatsuba_table_has_no_part_in_the_workspace_calls(drive):
+    n, products = 65536, 16
+    calls = []
+    for depth in (0, 1, 3, binding.KARATSUBA_BUILTIN):
+        for word, fn, mod in ((8, "polymul_negacyclic_u64_workspace", [GOLDILOCKS]),
+                              (4, "polymul_negacyclic_rns_workspace", [{"u32": [Q30]}, 1])):
+            size = 4 * n * products * word
+            calls += [call("polymul_tune_set_karatsuba", n, products, word, depth),
+                      call(fn, A, B, C, n, *mod, products, W, size, None)]
+    for got in drive(calls)[1::2]:
+        assert got["status"] == 0
+        assert ["pt_outer_forward" in got["launches"][0][0], "pt_outer_inverse" in got["launches"][2][0],
+                len(got["launches"])] == [True, True, 3]
+
+
+def test_workspace_arguments(drive):
+    EINVAL, EALIAS = 1, 2
+    n, need = 16384, 4 * 16384 * 2 * 4
+    rns = lambda ws, size, q=Q30, L=1, n=n, a=A, c=C: call(
+        "polymul_negacyclic_rns_workspace", a, B, c, n, {"u32": [q] * L}, L, 2 // L, ws, size, None)
+    u64 = lambda ws, size, q=GOLDILOCKS: call("polymul_negacyclic_u64_workspace", A, B, C, 8192, q, 4, ws, size, None)
+    cases = [
+        (rns(W, need), 0), (rns(W, need, L=2), 0), (rns(W, need - 1), EINVAL), (rns(W + 8, need), EINVAL),
+        (rns(None, need), EINVAL), (rns(A + 16, need), EALIAS), (rns(C - 16, need), EALIAS), (rns(W, need, a=C + 16), EALIAS),
+        (rns(W, need, q=1), EINVAL), (rns(W, need, n=10000), EINVAL),
+        (rns(None, 0, q=EVEN), 0), (rns(None, 0, n=8192), 0),  # no workspace in use
+        (u64(W, 4 * 8192 * 4 * 8), 0), (u64(W, 4 * 8192 * 4 * 8 - 1), EINVAL), (u64(B, 4 * 8192 * 4 * 8), EALIAS),
+        (u64(None, 0, q=1 << 40), 0), (u64(None, 0, q=0), EINVAL),
+        (call("polymul_workspace_size", 100, 1, 4, {"out": 64}), EINVAL),
+        (call("polymul_workspace_size", 16384, 1, 2, {"out": 64}), EINVAL),
+        (call("polymul_workspace_size", 16384, 1 << 41, 4, {"out": 64}), EINVAL),
+    ]
+    for (c, want), got in zip(cases, drive([c for c, _ in cases])):
+        assert got["status"] == want, c
+    for n in (4096, 8192):
+        assert binding.polymul_workspace_size(n, 7, 4) == 0
+    assert binding.polymul_workspace_size(4096, 7, 8) == 0 and binding.polymul_workspace_size(8192, 7, 8) == 4 * 8192 * 7 * 8
