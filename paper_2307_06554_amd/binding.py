@@ -184,6 +184,21 @@ def _large(n, rows, nbytes):
     return rows > 0 and _WS_DEGREE[nbytes] <= n <= 65536 and n & (n - 1) == 0
 
 
+def _scratch(nbytes, device):
+    """Bytes of torch memory, asked for in the relaxed capture mode: where torch has to call hipMalloc
+    and some other stream of the process is being captured (in the default, global mode), both the
+    allocation and that capture would otherwise fail, though the call is no part of it."""
+    import torch
+    exchange = load_library().hipThreadExchangeStreamCaptureMode  # of the HIP runtime the library is bound to
+    mode = ctypes.c_int(2)  # hipStreamCaptureModeRelaxed; each exchange leaves the mode before it here
+    relaxed = exchange(ctypes.byref(mode)) == 0
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    finally:
+        if relaxed:
+            exchange(ctypes.byref(mode))
+
+
 def _through_workspace(name, nbytes, a, b, c, n, rows, stream, call):
     """call(a, b, c pointers, rows, workspace pointer, its bytes, stream) over the `rows` rows of
     a, b and c, as many at a time as _WS_BYTES of workspace hold; False where nothing
@@ -205,7 +220,7 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, call):
     chunk = max(1, min(rows, _WS_BYTES // per_row))
     need = chunk * per_row
     try:
-        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+        ws = _scratch(need, a.device)
     except torch.cuda.OutOfMemoryError:
         return False
     for r in range(0, rows, chunk):

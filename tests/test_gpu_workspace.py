@@ -83,3 +83,40 @@ def test_captured_call_asks_for_none(asked):
         c.fill_(-1)
         graph.replay()
         check(c, want, "replay")
+
+
+@pytest.mark.parametrize("in_thread", [False, True], ids=["same thread", "other thread"])
+def test_call_beside_a_capture(in_thread):
+    """A direct call on one stream while another one is captured in the default, global mode: torch has
+    to call hipMalloc for the workspace, and neither the call nor the capture minds."""
+    import threading
+    n, batch = 65536, 16
+    rng = np.random.default_rng(3)
+    da, db = (to_dev(rng.integers(0, GOLD, size=(batch, n), dtype=np.uint64)) for _ in range(2))
+    want = pm.polymul_negacyclic_u64(da, db, GOLD)
+    c, x, side, errors = torch.empty_like(da), torch.zeros(64, device="cuda"), torch.cuda.Stream(), []
+
+    def call():
+        try:
+            with torch.cuda.stream(side):
+                pm.polymul_negacyclic_u64(da, db, GOLD, out=c)
+        except Exception as e:
+            errors.append(e)
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):  # empties torch's cache first
+        x.add_(1)
+        if in_thread:
+            thread = threading.Thread(target=call)
+            thread.start()
+            thread.join()
+        else:
+            call()
+    assert not errors
+    side.synchronize()
+    assert torch.equal(c, want)
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert x.eq(3).all()
