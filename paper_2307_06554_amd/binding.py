@@ -218,11 +218,15 @@ def _through_workspace(name, nbytes, a, b, c, n, rows, stream, call):
     row = total // rows
     per_row = polymul_workspace_size(n, row // (n * nbytes), nbytes)
     chunk = max(1, min(rows, _WS_BYTES // per_row))
-    need = chunk * per_row
-    try:
-        ws = _scratch(need, a.device)
-    except torch.cuda.OutOfMemoryError:
-        return False
+    while True:
+        need = chunk * per_row
+        try:
+            ws = _scratch(need, a.device)
+            break
+        except torch.cuda.OutOfMemoryError:
+            if chunk == 1:
+                return False
+            chunk = (chunk + 3) // 4
     for r in range(0, rows, chunk):
         _check(call(pa + r * row, pb + r * row, pc + r * row, min(chunk, rows - r), ws.data_ptr(), need, raw), name)
     return True

@@ -120,3 +120,17 @@ def test_call_beside_a_capture(in_thread):
         graph.replay()
     torch.cuda.synchronize()
     assert x.eq(3).all()
+
+
+def test_little_room(asked):
+    """Where there is no room for a chunk, smaller ones before the call goes without a workspace."""
+    n, row = 8192, 4 * 8192 * 8
+    a, b, want = operands(n, 11, GOLD, 8)
+    da, db = to_dev(a), to_dev(b)
+    asked.limit = row
+    check(pm.polymul_negacyclic_u64(da, db, GOLD), want, "rows one by one")
+    assert asked == [11 * row, 3 * row, row]
+    asked.clear()
+    asked.limit = 0
+    check(pm.polymul_negacyclic_u64(da, db, GOLD), want, "no workspace")
+    assert asked == [11 * row, 3 * row, row]
