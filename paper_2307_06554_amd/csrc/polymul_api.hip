@@ -642,15 +642,33 @@ bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {  // M = 256
   return true;
 }
 
+// launch(parameters, workgroups) over all of P's products.  A grid holds fewer than 2^32 threads, which
+// arrays of 128 GiB reach: the products then go in several launches, each of whole rounds over the
+// moduli so that the next one's are at a fixed distance.
+template <typename W, typename Launch>
+polymul_status ptrans_launches(const PtParams<W>& P, uint32_t group, uint32_t threads, Launch launch) {
+  const uint64_t round = (uint64_t)P.lc * P.lrep, most = 0xFFFFFFFFull / threads * group / round * round;
+  if (P.nprod <= most) return launch(P, (uint32_t)((P.nprod + group - 1) / group));
+  const uint64_t words = most / P.lc * P.nq_total * P.n;
+  PtParams<W> Q = P;
+  for (uint64_t left = P.nprod; left; left -= Q.nprod) {
+    Q.nprod = std::min(left, most);
+    const polymul_status st = launch(Q, (uint32_t)((Q.nprod + group - 1) / group));
+    if (st != POLYMUL_OK) return st;
+    Q.a += words;
+    Q.c += words;
+    if (!Q.b_shared) Q.b += words;
+  }
+  return POLYMUL_OK;
+}
+
 template <typename W, int L, int LK, int C = 1>
 polymul_status launch_ptrans(const PtParams<W>& P, hipStream_t s) {
   if (allow_lds<k_ptrans<W, L, LK, C>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
-  constexpr uint32_t G = 16 >> LK;
-  const uint64_t groups = (P.nprod + G - 1) / G;
-  if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
-  hipLaunchKernelGGL((ptrans_kernel<W, L, LK, C>), dim3((uint32_t)groups), dim3(512 * C), (pt_lds_bytes<W, L, C, 2>()), s,
-                     P);
-  return launch_status();
+  return ptrans_launches(P, 16 >> LK, 512 * C, [s](const PtParams<W>& Q, uint32_t groups) {
+    hipLaunchKernelGGL((ptrans_kernel<W, L, LK, C>), dim3(groups), dim3(512 * C), (pt_lds_bytes<W, L, C, 2>()), s, Q);
+    return launch_status();
+  });
 }
 template <typename W, int L>
 polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
@@ -713,11 +731,10 @@ bool ptrans_takes_cyclic(uint32_t n, const uint32_t* qs, uint32_t lc, int L, uin
 template <int L, int LK, int C = 1>
 polymul_status launch_ptrans_cyclic(const PtParams<uint32_t>& P, hipStream_t s) {
   if (allow_lds<k_ptrans_cyclic<L, LK, C>>() != POLYMUL_OK) return POLYMUL_EDEVICE;
-  constexpr uint32_t G = 16 >> LK;
-  const uint64_t groups = (P.nprod + G - 1) / G;
-  if (groups > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
-  hipLaunchKernelGGL((ptrans_cyclic_kernel<L, LK, C>), dim3((uint32_t)groups), dim3(512 * C), (pt_cyclic_lds<L, C>()), s, P);
-  return launch_status();
+  return ptrans_launches(P, 16 >> LK, 512 * C, [s](const PtParams<uint32_t>& Q, uint32_t groups) {
+    hipLaunchKernelGGL((ptrans_cyclic_kernel<L, LK, C>), dim3(groups), dim3(512 * C), (pt_cyclic_lds<L, C>()), s, Q);
+    return launch_status();
+  });
 }
 template <int L>
 polymul_status launch_ptrans_cyclic_L(const PtParams<uint32_t>& P, hipStream_t s) {

@@ -104,3 +104,34 @@ def test_workspace_arguments(drive):
     for n in (4096, 8192):
         assert binding.polymul_workspace_size(n, 7, 4) == 0
     assert binding.polymul_workspace_size(4096, 7, 8) == 0 and binding.polymul_workspace_size(8192, 7, 8) == 4 * 8192 * 7 * 8
+
+
+# ------------------------------------------------------------------ launches the hardware holds
+BIG = [  # entry point, its arguments after a, b, c, degree, words per product's group, products
+    ("polymul_negacyclic_shared", [4096, Q30], 1, (1 << 23) + 100),
+    ("polymul_negacyclic_shared", [8192, Q30], 1, (1 << 22) + 3),
+    ("polymul_negacyclic_shared", [1024, Q30], 1, (1 << 25) + 5),
+    ("polymul_negacyclic_rns_shared", [2048, {"u32": [Q30, 12289, 65537]}, 3], 3, (1 << 24) // 3 + 7),
+    ("polymul_cyclic", [4096, Q30], 1, (1 << 23) + 1),
+    ("polymul_cyclic", [8192, Q30], 1, (1 << 22) + 1),
+]
+
+
+@pytest.mark.parametrize("fn,args,channels,batch", BIG, ids=[f"{f[8:]}-{a[0]}" for f, a, _, _ in BIG])
+def test_arrays_beyond_one_grid(drive, fn, args, channels, batch):
+    """Arrays of more than 128 GiB (a and c, or one operand squared, fit the memory): more
+    work-items than a launch holds, so several launches over consecutive products."""
+    n = args[0]
+    b = A if fn == "polymul_cyclic" else B
+    got = drive([call(fn, A, b, C, *args, batch, None)])[0]
+    assert got["status"] == 0
+    at = 0
+    for launch in got["launches"]:
+        assert "ptrans" in launch[0]
+        grid, block = int(launch[1]), int(launch[3])
+        a, bb, c, nprod = (int(v) for v in launch[5:9])
+        assert grid * block < 1 << 32
+        assert (a, c) == (A + 4 * n * at, C + 4 * n * at) and bb == (b if b == B else a)
+        assert nprod % channels == 0 and grid * max(1, 4096 // n) >= nprod > 0
+        at += nprod
+    assert at == batch * channels and len(got["launches"]) == 2
