@@ -1127,11 +1127,24 @@ std::atomic<uint32_t> g_plan_stream_pct{125};
 // workgroup on its CU, where a group of n = 4096 with 8192 takes 38 us).  A product of n = 8192 is
 // three items, the sub-products of one Karatsuba level, and a share of the combine kernel: as
 // K-split runs on tiles it took four of 33 us, the last items of the uneven batch by far.  The
-// sub-products live in the plan's buffer (1.5 times c), so groups that would need more than
-// 256 MiB of it stay on the tiles.
-bool plan_ptrans(uint32_t n, uint64_t count, uint32_t q, int L) {
-  if (n == 8192 && count > (256u << 20) / (3 * 4096 * 4)) return false;
-  return L == 4 && ptrans_takes(n, &q, 1, L, count);
+// sub-products live in the plan's buffer (1.5 times c): groups that would take it beyond 256 MiB stay
+// on the tiles, and so do all of that degree (sub_products false) where the buffer finds no room.
+// Decided once per plan, whatever another thread does to the tile table meanwhile.
+std::vector<char> plan_routes(const polymul_group* groups, uint32_t ngroups, bool sub_products) {
+  std::vector<char> pt(ngroups, 0);
+  uint64_t words = 0;
+  for (uint32_t g = 0; g < ngroups; ++g) {
+    const polymul_group& G = groups[g];
+    const uint32_t n = (uint32_t)G.n, q = (uint32_t)G.q;
+    if (G.elem_bytes != 4 || G.count == 0 || limbs32(&q, 1) != 4 || !ptrans_takes(n, &q, 1, 4, G.count)) continue;
+    if (n == 8192) {
+      const uint64_t most = (64u << 20) / (3 * 4096), sub = 3 * 4096 * G.count;
+      if (!sub_products || G.count > most || words + sub > 64u << 20) continue;
+      words += sub;
+    }
+    pt[g] = 1;
+  }
+  return pt;
 }
 constexpr uint64_t kPtItemCost = 5632;
 uint64_t plan_ptrans_items(uint32_t n, uint64_t count) { return n == 8192 ? 3 * count : (count * n + 4095) / 4096; }
@@ -1154,9 +1167,9 @@ uint64_t item_cost(const GroupJob& j) {
 
 // The same for one unsplit item of a 32-bit group on its default route (resident for
 // n in [4, 8192]: beyond 4096 only as K-split runs, else streamed), and the number of
-// such items.
-void default_cost(uint32_t n, uint32_t q, uint64_t count, int L, uint64_t* items, uint64_t* cost) {
-  if (plan_ptrans(n, count, q, L)) {
+// such items.  pt: the group goes through the transform.
+void default_cost(uint32_t n, bool pt, uint64_t count, int L, uint64_t* items, uint64_t* cost) {
+  if (pt) {
     *items = plan_ptrans_items(n, count);
     *cost = kPtItemCost;
   } else if (n >= 64 && plan_tile(n, L) == 16) {
@@ -1208,6 +1221,196 @@ bool k_window_split(GroupJob& job, uint64_t ci, uint64_t share, uint32_t* lds) {
   P.slots = 1;
   *lds = slot;
   return true;
+}
+
+// Device memory for a plan; a failure is not left for the next launch to report.
+bool plan_malloc(void** out, uint64_t bytes) {
+  if (hipMalloc(out, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Jobs, work list, buffers and graph of validated groups into an empty plan.
+polymul_status plan_build(polymul_plan* p, const polymul_group* groups, uint32_t ngroups, bool sub_products) {
+  std::vector<GroupJob> jobs;
+  std::vector<WorkItem> items;
+  const std::vector<char> routes = plan_routes(groups, ngroups, sub_products);
+  // Balance (paper Sec. 3 notes the TPU's lack of fine control): the persistent grid
+  // holds two workgroups per CU; the items of a 32-bit group that would cost more
+  // than a CU's even share of the total (two workgroups' shares: finer runs pay more
+  // staging than they save) have their K range cut into runs (resident groups of one
+  // product, or streamed blocks), whose residues a second kernel adds up mod q.
+  uint64_t total_cost = 0;
+  for (uint32_t g = 0; g < ngroups; ++g) {
+    if (groups[g].elem_bytes != 4 || groups[g].count == 0) continue;
+    const uint32_t q32 = (uint32_t)groups[g].q;
+    uint64_t ni, ci;
+    default_cost((uint32_t)groups[g].n, routes[g], groups[g].count, limbs32(&q32, 1), &ni, &ci);
+    total_cost += ni * ci;
+  }
+  const uint64_t share = std::max<uint64_t>(
+      64, total_cost / device_cus() * g_plan_share_pct.load(std::memory_order_relaxed) / 100);
+  uint64_t part_words = 0;
+  for (uint32_t g = 0; g < ngroups; ++g) {
+    const polymul_group& G = groups[g];
+    if (G.count == 0) continue;
+    const uint32_t n = (uint32_t)G.n;
+    if (G.elem_bytes == 8) {
+      StreamParams sp;
+      uint32_t lds;
+      const int L = limbs64(&G.q, 1);
+      polymul_status st = fill_stream(sp, G.a, G.b, G.c, n, &G.q, 1, 1, 0, G.count, L, &lds);
+      if (st != POLYMUL_OK) return st;
+      p->wide.push_back(sp);
+      p->wide_lds.push_back(lds);
+      p->wide_L.push_back(L);
+      continue;
+    }
+    GroupJob job{};
+    const uint32_t q32 = (uint32_t)G.q;
+    uint32_t lds = 0;
+    polymul_status st;
+    uint64_t ni, ci;
+    const int Lg = limbs32(&q32, 1);
+    default_cost(n, routes[g], G.count, Lg, &ni, &ci);
+    const bool split = ci > share;
+    job.L = (uint32_t)Lg;
+    if (routes[g]) {
+      job.kind = kJobPtrans;
+      p->transform = true;
+      if (n == 8192) {
+        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, nullptr, 4096, &q32, 1, 1, 0, 3 * G.count, Lg, 1,
+                    false, 1);
+        job.pp.kara = 1;
+        job.pp.c = (uint32_t*)(uintptr_t)part_words;  // an offset until the buffer exists
+        part_words += 3 * G.count * 4096;
+        KaraParams K{};
+        K.c = (uint32_t*)G.c;
+        K.nprod = G.count; K.n = n; K.np = 4096; K.depth = 1; K.nsub = 3; K.L = 1;
+        K.mods[0] = make_mod32(q32, Lg);
+        p->kara.push_back(K);
+      } else {
+        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0, G.count, Lg, 1,
+                    false, 1);
+      }
+      lds = pt_lds_bytes<uint32_t, 4, 1, 1>();
+      st = POLYMUL_OK;
+    } else if (n >= 64 && plan_tile(n, Lg) == 16) {
+      job.kind = kJobSmall;
+      st = fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
+                       G.count, Lg, 16, &lds);
+      job.rp.slots = plan_small_slots(job.rp.slot_bytes);
+      lds = job.rp.slots * job.rp.slot_bytes + kSlots16 * (uint32_t)sizeof(Slot16);
+    } else if (n >= 4 && n <= 4096) {
+      job.kind = kJobResident;
+      st = fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
+                       G.count, Lg, plan_tile(n, Lg), &lds);
+      if (st == POLYMUL_OK && split && k_window_split(job, ci, share, &lds)) {
+        // an offset for now; turned into a device pointer once the buffer exists
+        job.rp.part_ws = (uint32_t*)(uintptr_t)part_words;
+        part_words += (uint64_t)job.rp.kparts * G.count * n;
+      }
+    } else if (split && n <= 8192 &&
+               fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
+                           G.count, Lg, plan_tile(n, Lg), &lds) == POLYMUL_OK &&
+               k_window_split(job, ci, share, &lds)) {
+      // whole products too large for two workgroups per CU, K-split into windowed runs
+      job.kind = kJobResident;
+      st = POLYMUL_OK;
+      job.rp.part_ws = (uint32_t*)(uintptr_t)part_words;
+      part_words += (uint64_t)job.rp.kparts * G.count * n;
+    } else {
+      job.kind = kJobStream;
+      const uint64_t q64 = G.q;
+      st = fill_stream(job.sp, G.a, G.b, G.c, n, &q64, 1, 1, 0, G.count, 4, &lds);
+      if (st == POLYMUL_OK && split) {
+        uint32_t k = 1;
+        while (k < job.sp.nchunks && ci / k > share) k *= 2;
+        job.sp.kparts = k;
+        if (k > 1) {
+          job.sp.part_ws = (void*)(uintptr_t)part_words;
+          part_words += (uint64_t)k * G.count * n;
+        }
+      }
+    }
+    if (st != POLYMUL_OK) return st;
+    p->lds = std::max(p->lds, lds);
+    const uint32_t jid = (uint32_t)jobs.size();
+    const uint64_t cnt = job.kind == kJobPtrans     ? ni
+                         : job.kind == kJobSmall    ? (G.count + job.rp.slots - 1) / job.rp.slots
+                         : job.kind == kJobResident ? ((G.count << job.rp.log2U) + 3) / 4 * job.rp.kparts
+                                                    : G.count * job.sp.ublocks * job.sp.kparts;
+    if (cnt + items.size() > 0xFFFFFFFFull) return POLYMUL_EUNSUPPORTED;
+    for (uint64_t i = 0; i < cnt; ++i) items.push_back(WorkItem{jid, (uint32_t)i});
+    jobs.push_back(job);
+  }
+  // largest items first
+  std::stable_sort(items.begin(), items.end(), [&](const WorkItem& x, const WorkItem& y) {
+    return item_cost(jobs[x.group]) > item_cost(jobs[y.group]);
+  });
+  p->nitems = (uint32_t)items.size();
+  if (p->nitems) {
+    if (!plan_malloc((void**)&p->d_jobs, jobs.size() * sizeof(GroupJob)) ||
+        !plan_malloc((void**)&p->d_items, items.size() * sizeof(WorkItem)) || !plan_malloc((void**)&p->d_counter, 256))
+      return POLYMUL_ENOMEM;
+    if (part_words) {
+      if (!plan_malloc(&p->d_part_ws, part_words * 4)) return POLYMUL_ENOMEM;
+      size_t nk = 0;
+      for (GroupJob& j : jobs) {
+        if (j.kind == kJobPtrans && j.pp.kara) {
+          j.pp.c = (uint32_t*)p->d_part_ws + (uintptr_t)j.pp.c;
+          p->kara[nk++].sc = j.pp.c;
+        }
+        if (j.kind == kJobStream && j.sp.kparts > 1) {
+          j.sp.part_ws = (uint32_t*)p->d_part_ws + (uintptr_t)j.sp.part_ws;
+          p->segs.push_back({(const uint32_t*)j.sp.part_ws, (uint32_t*)j.sp.c, j.sp.nprod * j.sp.n, j.sp.kparts,
+                             0, make_mod32((uint32_t)j.sp.mods[0].q, 4)});
+        }
+        if (j.kind == kJobResident && j.rp.kparts > 1) {
+          j.rp.part_ws = (uint32_t*)p->d_part_ws + (uintptr_t)j.rp.part_ws;
+          p->segs.push_back({j.rp.part_ws, j.rp.c, j.rp.nprod * j.rp.n, j.rp.kparts, 0, j.rp.mods[0]});
+        }
+      }
+      uint64_t blocks = 0;
+      for (SplitSeg& sg : p->segs) {
+        sg.first_block = (uint32_t)blocks;
+        blocks += (sg.words / 4 + 255) / 256;
+      }
+      if (blocks > 0x7FFFFFFFull) return POLYMUL_EUNSUPPORTED;
+      p->sum_blocks = (uint32_t)blocks;
+      if (!p->segs.empty() && !plan_malloc((void**)&p->d_segs, p->segs.size() * sizeof(SplitSeg)))
+        return POLYMUL_ENOMEM;
+    }
+    hipError_t e = hipMemcpy(p->d_jobs, jobs.data(), jobs.size() * sizeof(GroupJob), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(p->d_items, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !p->segs.empty())
+      e = hipMemcpy(p->d_segs, p->segs.data(), p->segs.size() * sizeof(SplitSeg), hipMemcpyHostToDevice);
+    // the grouped kernel leaves its counters at zero; they start there (set outside any
+    // capture, and finished before the plan is returned: the caller's stream need not
+    // be ordered after the null stream the memset runs on)
+    if (e == hipSuccess) e = hipMemset(p->d_counter, 0, 2 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy (plan tables)");
+    // persistent grid: as many workgroups as fit at once (two per CU within the register budget)
+    const uint32_t per_cu = std::max(1u, std::min(2u, kMaxLds / std::max(p->lds, 1u)));
+    p->grid = std::min<uint64_t>(p->nitems, (uint64_t)device_cus() * per_cu);
+  }
+  if (plan_attrs() != POLYMUL_OK) return POLYMUL_EDEVICE;
+  if (p->use_graph && (p->nitems || !p->wide.empty())) {
+    hipError_t e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamCreateWithFlags");
+    e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
+    const polymul_status st = plan_launch(p, p->cap_stream);
+    hipGraph_t graph = nullptr;
+    e = hipStreamEndCapture(p->cap_stream, &graph);
+    p->graph = graph;
+    if (st != POLYMUL_OK || e != hipSuccess || !graph)
+      return e != hipSuccess ? hip_fail(e, "hipStreamEndCapture") : POLYMUL_EDEVICE;
+    e = hipGraphInstantiate(&p->exec, graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
+  }
+  return POLYMUL_OK;
 }
 
 }  // namespace
@@ -1299,201 +1502,21 @@ polymul_status polymul_plan_create(polymul_plan** plan, const polymul_group* gro
     polymul_status st = check_arrays(G.a, G.b, G.c, G.n, G.count, 1, G.elem_bytes, &bytes);
     if (st != POLYMUL_OK) return st;
   }
-  polymul_plan* p = new (std::nothrow) polymul_plan();
-  if (!p) return POLYMUL_ENOMEM;
-  p->use_graph = !(flags & POLYMUL_PLAN_NO_GRAPH);
-  std::vector<GroupJob> jobs;
-  std::vector<WorkItem> items;
-  // Balance (paper Sec. 3 notes the TPU's lack of fine control): the persistent grid
-  // holds two workgroups per CU; the items of a 32-bit group that would cost more
-  // than a CU's even share of the total (two workgroups' shares: finer runs pay more
-  // staging than they save) have their K range cut into runs (resident groups of one
-  // product, or streamed blocks), whose residues a second kernel adds up mod q.
-  uint64_t total_cost = 0;
-  for (uint32_t g = 0; g < ngroups; ++g) {
-    if (groups[g].elem_bytes != 4 || groups[g].count == 0) continue;
-    const uint32_t q32 = (uint32_t)groups[g].q;
-    uint64_t ni, ci;
-    default_cost((uint32_t)groups[g].n, q32, groups[g].count, limbs32(&q32, 1), &ni, &ci);
-    total_cost += ni * ci;
-  }
-  const uint64_t share = std::max<uint64_t>(
-      64, total_cost / device_cus() * g_plan_share_pct.load(std::memory_order_relaxed) / 100);
-  uint64_t part_words = 0;
-  for (uint32_t g = 0; g < ngroups; ++g) {
-    const polymul_group& G = groups[g];
-    if (G.count == 0) continue;
-    const uint32_t n = (uint32_t)G.n;
-    if (G.elem_bytes == 8) {
-      StreamParams sp;
-      uint32_t lds;
-      const int L = limbs64(&G.q, 1);
-      polymul_status st = fill_stream(sp, G.a, G.b, G.c, n, &G.q, 1, 1, 0, G.count, L, &lds);
-      if (st != POLYMUL_OK) { plan_free(p); return st; }
-      p->wide.push_back(sp);
-      p->wide_lds.push_back(lds);
-      p->wide_L.push_back(L);
-      continue;
+  // without room for the sub-products of n = 8192, once more with those groups on the tiles
+  for (int sub_products = 1; sub_products >= 0; --sub_products) {
+    polymul_plan* p = new (std::nothrow) polymul_plan();
+    if (!p) return POLYMUL_ENOMEM;
+    p->use_graph = !(flags & POLYMUL_PLAN_NO_GRAPH);
+    const polymul_status st = plan_build(p, groups, ngroups, sub_products != 0);
+    if (st == POLYMUL_OK) {
+      *plan = p;
+      return st;
     }
-    GroupJob job{};
-    const uint32_t q32 = (uint32_t)G.q;
-    uint32_t lds = 0;
-    polymul_status st;
-    uint64_t ni, ci;
-    const int Lg = limbs32(&q32, 1);
-    default_cost(n, q32, G.count, Lg, &ni, &ci);
-    const bool split = ci > share;
-    job.L = (uint32_t)Lg;
-    if (plan_ptrans(n, G.count, q32, Lg)) {
-      job.kind = kJobPtrans;
-      p->transform = true;
-      if (n == 8192) {
-        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, nullptr, 4096, &q32, 1, 1, 0, 3 * G.count, Lg, 1,
-                    false, 1);
-        job.pp.kara = 1;
-        job.pp.c = (uint32_t*)(uintptr_t)part_words;  // an offset until the buffer exists
-        part_words += 3 * G.count * 4096;
-        KaraParams K{};
-        K.c = (uint32_t*)G.c;
-        K.nprod = G.count; K.n = n; K.np = 4096; K.depth = 1; K.nsub = 3; K.L = 1;
-        K.mods[0] = make_mod32(q32, Lg);
-        p->kara.push_back(K);
-      } else {
-        fill_ptrans(job.pp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0, G.count, Lg, 1,
-                    false, 1);
-      }
-      lds = pt_lds_bytes<uint32_t, 4, 1, 1>();
-      st = POLYMUL_OK;
-    } else if (n >= 64 && plan_tile(n, Lg) == 16) {
-      job.kind = kJobSmall;
-      st = fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
-                       G.count, Lg, 16, &lds);
-      job.rp.slots = plan_small_slots(job.rp.slot_bytes);
-      lds = job.rp.slots * job.rp.slot_bytes + kSlots16 * (uint32_t)sizeof(Slot16);
-    } else if (n >= 4 && n <= 4096) {
-      job.kind = kJobResident;
-      st = fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
-                       G.count, Lg, plan_tile(n, Lg), &lds);
-      if (st == POLYMUL_OK && split && k_window_split(job, ci, share, &lds)) {
-        // an offset for now; turned into a device pointer once the buffer exists
-        job.rp.part_ws = (uint32_t*)(uintptr_t)part_words;
-        part_words += (uint64_t)job.rp.kparts * G.count * n;
-      }
-    } else if (split && n <= 8192 &&
-               fill_mfma32(job.rp, (const uint32_t*)G.a, (const uint32_t*)G.b, (uint32_t*)G.c, n, &q32, 1, 1, 0,
-                           G.count, Lg, plan_tile(n, Lg), &lds) == POLYMUL_OK &&
-               k_window_split(job, ci, share, &lds)) {
-      // whole products too large for two workgroups per CU, K-split into windowed runs
-      job.kind = kJobResident;
-      st = POLYMUL_OK;
-      job.rp.part_ws = (uint32_t*)(uintptr_t)part_words;
-      part_words += (uint64_t)job.rp.kparts * G.count * n;
-    } else {
-      job.kind = kJobStream;
-      const uint64_t q64 = G.q;
-      st = fill_stream(job.sp, G.a, G.b, G.c, n, &q64, 1, 1, 0, G.count, 4, &lds);
-      if (st == POLYMUL_OK && split) {
-        uint32_t k = 1;
-        while (k < job.sp.nchunks && ci / k > share) k *= 2;
-        job.sp.kparts = k;
-        if (k > 1) {
-          job.sp.part_ws = (void*)(uintptr_t)part_words;
-          part_words += (uint64_t)k * G.count * n;
-        }
-      }
-    }
-    if (st != POLYMUL_OK) { plan_free(p); return st; }
-    p->lds = std::max(p->lds, lds);
-    const uint32_t jid = (uint32_t)jobs.size();
-    const uint64_t cnt = job.kind == kJobPtrans     ? ni
-                         : job.kind == kJobSmall    ? (G.count + job.rp.slots - 1) / job.rp.slots
-                         : job.kind == kJobResident ? ((G.count << job.rp.log2U) + 3) / 4 * job.rp.kparts
-                                                    : G.count * job.sp.ublocks * job.sp.kparts;
-    if (cnt + items.size() > 0xFFFFFFFFull) { plan_free(p); return POLYMUL_EUNSUPPORTED; }
-    for (uint64_t i = 0; i < cnt; ++i) items.push_back(WorkItem{jid, (uint32_t)i});
-    jobs.push_back(job);
-  }
-  // largest items first
-  std::stable_sort(items.begin(), items.end(), [&](const WorkItem& x, const WorkItem& y) {
-    return item_cost(jobs[x.group]) > item_cost(jobs[y.group]);
-  });
-  p->nitems = (uint32_t)items.size();
-  if (p->nitems) {
-    if (hipMalloc((void**)&p->d_jobs, jobs.size() * sizeof(GroupJob)) != hipSuccess ||
-        hipMalloc((void**)&p->d_items, items.size() * sizeof(WorkItem)) != hipSuccess ||
-        hipMalloc((void**)&p->d_counter, 256) != hipSuccess) {
-      plan_free(p);
-      return POLYMUL_ENOMEM;
-    }
-    if (part_words) {
-      if (hipMalloc(&p->d_part_ws, part_words * 4) != hipSuccess) {
-        plan_free(p);
-        return POLYMUL_ENOMEM;
-      }
-      size_t nk = 0;
-      for (GroupJob& j : jobs) {
-        if (j.kind == kJobPtrans && j.pp.kara) {
-          j.pp.c = (uint32_t*)p->d_part_ws + (uintptr_t)j.pp.c;
-          p->kara[nk++].sc = j.pp.c;
-        }
-        if (j.kind == kJobStream && j.sp.kparts > 1) {
-          j.sp.part_ws = (uint32_t*)p->d_part_ws + (uintptr_t)j.sp.part_ws;
-          p->segs.push_back({(const uint32_t*)j.sp.part_ws, (uint32_t*)j.sp.c, j.sp.nprod * j.sp.n, j.sp.kparts,
-                             0, make_mod32((uint32_t)j.sp.mods[0].q, 4)});
-        }
-        if (j.kind == kJobResident && j.rp.kparts > 1) {
-          j.rp.part_ws = (uint32_t*)p->d_part_ws + (uintptr_t)j.rp.part_ws;
-          p->segs.push_back({j.rp.part_ws, j.rp.c, j.rp.nprod * j.rp.n, j.rp.kparts, 0, j.rp.mods[0]});
-        }
-      }
-      uint64_t blocks = 0;
-      for (SplitSeg& sg : p->segs) {
-        sg.first_block = (uint32_t)blocks;
-        blocks += (sg.words / 4 + 255) / 256;
-      }
-      if (blocks > 0x7FFFFFFFull) { plan_free(p); return POLYMUL_EUNSUPPORTED; }
-      p->sum_blocks = (uint32_t)blocks;
-      if (!p->segs.empty() && hipMalloc((void**)&p->d_segs, p->segs.size() * sizeof(SplitSeg)) != hipSuccess) {
-        plan_free(p);
-        return POLYMUL_ENOMEM;
-      }
-    }
-    hipError_t e = hipMemcpy(p->d_jobs, jobs.data(), jobs.size() * sizeof(GroupJob), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(p->d_items, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !p->segs.empty())
-      e = hipMemcpy(p->d_segs, p->segs.data(), p->segs.size() * sizeof(SplitSeg), hipMemcpyHostToDevice);
-    // the grouped kernel leaves its counters at zero; they start there (set outside any
-    // capture, and finished before the plan is returned: the caller's stream need not
-    // be ordered after the null stream the memset runs on)
-    if (e == hipSuccess) e = hipMemset(p->d_counter, 0, 2 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e != hipSuccess) { plan_free(p); return hip_fail(e, "hipMemcpy (plan tables)"); }
-    // persistent grid: as many workgroups as fit at once (two per CU within the register budget)
-    const uint32_t per_cu = std::max(1u, std::min(2u, kMaxLds / std::max(p->lds, 1u)));
-    p->grid = std::min<uint64_t>(p->nitems, (uint64_t)device_cus() * per_cu);
-  }
-  if (plan_attrs() != POLYMUL_OK) {
+    const bool again = st == POLYMUL_ENOMEM && !p->kara.empty();
     plan_free(p);
-    return POLYMUL_EDEVICE;
+    if (!again) return st;
   }
-  if (p->use_graph && (p->nitems || !p->wide.empty())) {
-    hipError_t e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
-    if (e != hipSuccess) { plan_free(p); return hip_fail(e, "hipStreamCreateWithFlags"); }
-    e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) { plan_free(p); return hip_fail(e, "hipStreamBeginCapture"); }
-    const polymul_status st = plan_launch(p, p->cap_stream);
-    hipGraph_t graph = nullptr;
-    e = hipStreamEndCapture(p->cap_stream, &graph);
-    p->graph = graph;
-    if (st != POLYMUL_OK || e != hipSuccess || !graph) {
-      plan_free(p);
-      return e != hipSuccess ? hip_fail(e, "hipStreamEndCapture") : POLYMUL_EDEVICE;
-    }
-    e = hipGraphInstantiate(&p->exec, graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) { plan_free(p); return hip_fail(e, "hipGraphInstantiate"); }
-  }
-  *plan = p;
-  return POLYMUL_OK;
+  return POLYMUL_ENOMEM;
 }
 
 polymul_status polymul_plan_execute(polymul_plan* plan, hipStream_t stream) {

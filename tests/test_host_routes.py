@@ -135,3 +135,27 @@ def test_arrays_beyond_one_grid(drive, fn, args, channels, batch):
         assert nprod % channels == 0 and grid * max(1, 4096 // n) >= nprod > 0
         at += nprod
     assert at == batch * channels and len(got["launches"]) == 2
+
+
+# ------------------------------------------------------------------------------------- plans
+MIB = 1 << 20
+
+
+def test_plan_buffer_is_bounded_over_all_groups(drive):
+    # each group's sub-products would take 234 MiB
+    got = drive([dict(plan=[[8192, Q30, 5000]] * 3)])[0]
+    assert got["status"] == 0 and got["leaked"] == 0
+    assert got["held"] < 258 * MIB
+    assert [k for k in kernels(got) if "grouped" in k] and sum("kara_combine" in k for k in kernels(got)) == 1
+
+
+@pytest.mark.parametrize("room", [4 * MIB, 0.01 * MIB], ids=["no room for sub-products", "no room at all"])
+def test_plan_without_room_for_sub_products(drive, room):
+    """A group of n = 8192 that needs a buffer on the transform and none on tiles takes those where
+    the buffer finds no room; the allocation that failed is not reported by the launches after it."""
+    plan = [[8192, Q30, 300], [1024, Q30, 64]]
+    got = drive([dict(plan=plan), dict(plan=plan, limit=int(room)), dict(plan=[[256, Q30, 1]])])
+    assert got[0]["held"] > 14 * MIB and sum("kara_combine" in k for k in kernels(got[0])) == 1
+    assert got[1]["status"] == (0 if room > MIB else 4)
+    assert not any("kara_combine" in k for k in kernels(got[1]))
+    assert [g["status"] for g in got[::2]] == [0, 0] and not any(g["leaked"] for g in got)
