@@ -1188,6 +1188,68 @@ void default_cost(uint32_t n, bool pt, uint64_t count, int L, uint64_t* items, u
   }
 }
 
+// An item longer than this is cut into runs (plan_build).
+uint64_t plan_share(uint64_t total_cost) {
+  return std::max<uint64_t>(64, total_cost / device_cus() * g_plan_share_pct.load(std::memory_order_relaxed) / 100);
+}
+// Runs that an item of `steps` K-steps and cost ci > share is cut into.
+uint32_t plan_runs(uint32_t steps, uint64_t ci, uint64_t share) {
+  uint32_t k = 1;
+  while (2 * k <= steps && ci / k > share) k *= 2;
+  return k;
+}
+
+// Light plans that leave the transform (pt: plan_routes') for tiles, where an item of it is the longest
+// of the plan and the tiles spread the same work over more CUs:
+//  - n = 1024 without a larger degree on it, tile items for up to three quarters of the CUs: one product
+//    18.9 us on tiles and 22.0 on the transform, 256 products 22.8 and 23.3, 768 23.9 and 23.9, 1000
+//    26.3 and 24.2;
+//  - n = 4096 and 8192, where the products' runs are at most one per CU and not so short that
+//    staging outweighs them: 3, 8 and 12 products of 8192 (runs of 512, 1024 and 2048 MFMAs) 26.6, 25.8
+//    and 28.4 us against 29.4 with the combine launch, 14 and 30 of 4096 22.8 and 23.8 against 24.6;
+//    just beside the rule 5 of 8192 (320 runs) 30.3, 16 (256 of 2048) 30.1, 7 and 45 of 4096 (runs of 256;
+//    360 runs) 25.3 and 29.7.  Groups of n <= 256 beside 8192 only count, with runs from 1024 on (6 products
+//    with 400 of 256: 26.6 and 29.4; 3 with 100, runs of 512: 29.9 and 29.1); with n = 512 it is the
+//    transform (6 with 100: 30.5 and 29.2).
+void plan_light(const polymul_group* groups, uint32_t ngroups, std::vector<char>& pt) {
+  bool any[3] = {false, false, false};  // on the transform: n = 1024, between, 8192
+  bool small = false, other = false;    // n <= 256; any other group that is not of 4096 or 8192 on the transform
+  uint64_t items1024 = 0, total = 0;
+  const auto cost = [&](uint32_t g, uint64_t* ni, uint64_t* ci) {
+    const uint32_t q = (uint32_t)groups[g].q;
+    default_cost((uint32_t)groups[g].n, false, groups[g].count, limbs32(&q, 1), ni, ci);
+  };
+  for (uint32_t g = 0; g < ngroups; ++g) {
+    const polymul_group& G = groups[g];
+    if (G.elem_bytes != 4 || G.count == 0) continue;
+    uint64_t ni, ci;
+    cost(g, &ni, &ci);
+    total += ni * ci;
+    if (pt[g]) any[G.n == 1024 ? 0 : G.n == 8192 ? 2 : 1] = true;
+    if (pt[g] && G.n == 1024) items1024 += ni;
+    if (G.n <= 256) small = true;
+    else other = other || !pt[g] || G.n < 4096;
+  }
+  if (any[0] && !any[1] && !any[2] && 4 * items1024 <= 3 * (uint64_t)device_cus()) pt.assign(ngroups, 0);
+  if (other || !(any[1] || any[2]) || (small && !any[2])) return;
+  const uint64_t share = plan_share(total);
+  uint64_t items = 0, longest = 0;
+  for (uint32_t g = 0; g < ngroups; ++g) {
+    if (groups[g].elem_bytes != 4 || groups[g].count == 0) continue;
+    uint64_t ni, ci;
+    cost(g, &ni, &ci);
+    if (pt[g]) {
+      const Geometry32 geo = geometry32((uint32_t)groups[g].n, plan_tile((uint32_t)groups[g].n, 4));
+      const uint32_t k = ci > share ? plan_runs(geo.r * geo.spd, ci, share) : 1;
+      ni *= k;
+      longest = std::max(longest, ci / k);
+      if (ci / k < (small ? 1024 : 512) || ci / k > (any[2] ? 2048 : 1024)) return;
+    }
+    items += ni;
+  }
+  if (items + (longest > 1024) <= device_cus()) pt.assign(ngroups, 0);
+}
+
 // K-split of a resident job whose item would cost `ci` > `share`: runs of K-steps
 // (a power of two of them) until a run costs at most the share.  Each run stages
 // only its K window (the K-steps' d range, D = d_hi - d_lo <= Dmax): ext positions
@@ -1198,9 +1260,7 @@ void default_cost(uint32_t n, bool pt, uint64_t count, int L, uint64_t* items, u
 bool k_window_split(GroupJob& job, uint64_t ci, uint64_t share, uint32_t* lds) {
   Mfma32Params& P = job.rp;
   if (P.log2U < 2 || P.n < 256 || P.t < 32) return false;
-  const uint32_t steps = P.r << P.log2spd;
-  uint32_t k = 1;
-  while (2 * k <= steps && ci / k > share) k *= 2;
+  const uint32_t steps = P.r << P.log2spd, k = plan_runs(steps, ci, share);
   if (k == 1) return false;
   uint32_t dmax = 0;
   for (uint32_t part = 0; part < k; ++part) {
@@ -1234,7 +1294,8 @@ bool plan_malloc(void** out, uint64_t bytes) {
 polymul_status plan_build(polymul_plan* p, const polymul_group* groups, uint32_t ngroups, bool sub_products) {
   std::vector<GroupJob> jobs;
   std::vector<WorkItem> items;
-  const std::vector<char> routes = plan_routes(groups, ngroups, sub_products);
+  std::vector<char> routes = plan_routes(groups, ngroups, sub_products);
+  plan_light(groups, ngroups, routes);
   // Balance (paper Sec. 3 notes the TPU's lack of fine control): the persistent grid
   // holds two workgroups per CU; the items of a 32-bit group that would cost more
   // than a CU's even share of the total (two workgroups' shares: finer runs pay more
@@ -1248,8 +1309,7 @@ polymul_status plan_build(polymul_plan* p, const polymul_group* groups, uint32_t
     default_cost((uint32_t)groups[g].n, routes[g], groups[g].count, limbs32(&q32, 1), &ni, &ci);
     total_cost += ni * ci;
   }
-  const uint64_t share = std::max<uint64_t>(
-      64, total_cost / device_cus() * g_plan_share_pct.load(std::memory_order_relaxed) / 100);
+  const uint64_t share = plan_share(total_cost);
   uint64_t part_words = 0;
   for (uint32_t g = 0; g < ngroups; ++g) {
     const polymul_group& G = groups[g];

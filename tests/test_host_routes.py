@@ -159,3 +159,23 @@ def test_plan_without_room_for_sub_products(drive, room):
     assert got[1]["status"] == (0 if room > MIB else 4)
     assert not any("kara_combine" in k for k in kernels(got[1]))
     assert [g["status"] for g in got[::2]] == [0, 0] and not any(g["leaked"] for g in got)
+
+
+@pytest.mark.parametrize("plan,transform", [
+    # n = 1024 alone or beside smaller degrees: tiles up to three quarters of the CUs
+    ([[1024, Q30, 1]], False), ([[1024, Q30, 768]], False), ([[1024, Q30, 769]], True),
+    ([[1024, Q30, 600], [1024, Q30 + 2, 600]], True), ([[1024, Q30, 8], [256, Q30, 100]], False),
+    ([[1024, Q30, 8], [2048, Q30, 1]], True), ([[1024, Q30, 8], [2048, 12289, 1]], False),
+    # n = 4096 and 8192: runs of whole products on tiles that fill at most every CU once
+    ([[8192, Q30, 1]], True), ([[8192, Q30, 3]], False), ([[8192, Q30, 5]], True), ([[8192, Q30, 8]], False),
+    ([[8192, Q30, 12]], False), ([[8192, Q30, 16]], True), ([[4096, Q30, 8]], True), ([[4096, Q30, 14]], False),
+    ([[4096, Q30, 30]], False), ([[4096, Q30, 45]], True), ([[8192, Q30, 6], [4096, Q30, 6]], False),
+    ([[8192, Q30, 8], [256, Q30, 1]], True), ([[8192, Q30, 7], [256, Q30, 100]], False),
+    ([[8192, Q30, 3], [256, Q30, 100]], True), ([[4096, Q30, 14], [256, Q30, 1]], True),
+    ([[8192, Q30, 7], [512, Q30, 10]], True), ([[8192, EVEN, 4], [8192, Q30, 4]], True),
+    ([[2048, Q30, 1]], True), ([[8192, Q30, 2], [1024, Q30, 1]], True),
+])
+def test_light_plans(drive, plan, transform):
+    got = drive([dict(plan=plan)])[0]
+    assert got["status"] == 0
+    assert ("grouped_kernelILb1" in got["launches"][0][0]) == transform
