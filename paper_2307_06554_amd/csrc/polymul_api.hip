@@ -944,6 +944,16 @@ polymul_status kara_workspace(uint64_t n, uint64_t products, uint32_t depth, uin
   return POLYMUL_OK;
 }
 
+// Calls of few products that depth 0 leaves to the built-in levels although the transform takes them,
+// us: n = 8192, whose transform has one workgroup per product, as long as the levels' 9 sub-products
+// of degree 2048, two per workgroup, find a CU each: one product 18.6 through the levels and 30.5
+// through the transform, 56 24.7 and 31.9, 60 31.8 and 32.0; with two limbs 15.0 and 19.2, 44 19.9 and
+// 20.0, 48 20.2 and 20.0.  n = 1024 at four limbs: two products 11.9 and 12.8, 192 13.4 and 13.7, 208 13.7
+// and 13.6.  At n = 2048 and 4096 one product takes 14.3 and 18.4 through them, 12.7 and 13.3 through it.
+bool kara_few(uint64_t n, int L, uint64_t products) {
+  return (n == 8192 && products <= (L == 2 ? 44 : 56)) || (n == 1024 && L == 4 && products <= 192);
+}
+
 // The RNS Karatsuba route on validated arguments with a workspace of at least
 // kara_workspace(n, batch * L, depth, 4) bytes: split, sub-products, combine.  choose: the
 // depth is the library's to pick and nothing was tuned, so the transform goes first (its 4 n
@@ -956,7 +966,7 @@ polymul_status run_rns_karatsuba(const uint32_t* a, const uint32_t* b, uint32_t*
     for (uint32_t l = 0; l < L; ++l) odd = odd && ptrans_modulus(q[l]);
     const int Lq = limbs32(q, L);
     if (odd && n > 8192) return run_outer32(a, b, c, n, q, L, batch, workspace, stream);
-    if (odd && n <= 8192 && ptrans_takes((uint32_t)n, q, L, Lq, batch * L))
+    if (odd && n <= 8192 && !kara_few(n, Lq, batch * L) && ptrans_takes((uint32_t)n, q, L, Lq, batch * L))
       return run_ptrans(a, b, c, (uint32_t)n, q, L, L, 0, batch * L, Lq, stream, 1, false);
   }
   const uint32_t nsub = depth == 1 ? 3 : depth == 2 ? 9 : 27;

@@ -46,3 +46,15 @@ def test_light_plans(shapes):
             for g, w in zip(held, want):
                 check(g[2], w, f"n={g[3]}, flags {flags}")
         plan.close()
+
+
+@pytest.mark.parametrize("n,L,batch", [(8192, 1, 3), (8192, 2, 28), (8192, 3, 19), (1024, 2, 96), (1024, 1, 193)])
+def test_depth_0_on_either_side_of_the_few(n, L, batch):
+    rng = np.random.default_rng([n, batch])
+    qs = [Q30, 12289, 0x7F7F7F7F][:L]
+    a, b = (np.stack([draw(rng, (batch, n), q) for q in qs], axis=1) for _ in range(2))
+    a[0], b[0] = np.array(qs, dtype=np.uint32)[:, None] - 1, draw(rng, (L, n), 1 << 32)
+    want = oracle.negacyclic_rns(a, b, qs)
+    da, db = to_dev(a), to_dev(b)
+    check(pm.polymul_negacyclic_rns_karatsuba(da, db, qs, 0), want, "caller's workspace")
+    check(pm.polymul_negacyclic_rns_karatsuba_noalloc(da, db, qs, 0), want, "the library's scratch")
