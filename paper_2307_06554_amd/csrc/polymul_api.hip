@@ -687,10 +687,14 @@ polymul_status launch_ptrans_L(const PtParams<W>& P, hipStream_t s) {
 // transform only halves the matrix work, two limbs (a quarter of the limb products) stay on
 // tiles: 8192 products 48 us against 51, one product 8.0 against 9.4; and so do a few products
 // at three limbs: one 10.2 against 12.1, from 8 on the transform is level (13.0 against 13.1)
-// or ahead (8192: 69 against 80).
-bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L, uint64_t nprod) {
+// or ahead (8192: 69 against 80).  With one b for the batch, whose rows the tiles' kernel stages
+// once, three limbs are level at 512 products (12.5 us each): 8 products 11.4 on tiles and 11.9
+// on the transform, 128 11.8 and 12.2, 1024 12.7 and 12.5, 8192 68 and 63.  Elsewhere the transform is
+// ahead from one product on: at four limbs n = 1024 12.6 against 12.8 us, n = 2048 12.8 against 21.0, at two
+// n = 2048 9.3 against 11.6.
+bool ptrans_takes(uint32_t n, const uint32_t* qs, uint32_t lc, int L, uint64_t nprod, bool b_shared = false) {
   if (n < 1024 || n > 8192) return false;
-  if (n == 1024 && (L == 2 || (L == 3 && nprod < 8))) return false;
+  if (n == 1024 && (L == 2 || (L == 3 && nprod < (b_shared ? 512 : 8)))) return false;
   if (g_tile[ilog2(n)][L].load(std::memory_order_relaxed)) return false;
   for (uint32_t i = 0; i < lc; ++i)
     if (!ptrans_modulus(qs[i])) return false;
@@ -875,7 +879,7 @@ polymul_status run_mfma32(const uint32_t* a, const uint32_t* b, uint32_t* c, uin
     return POLYMUL_OK;
   }
   const int L = limbs32(qs, lc);
-  if (!cyclic && ptrans_takes(n, qs, lc, L, nprod))
+  if (!cyclic && ptrans_takes(n, qs, lc, L, nprod, b_shared))
     return run_ptrans(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s, lrep, b_shared);
   if (cyclic && lrep == 1 && !b_shared && ptrans_takes_cyclic(n, qs, lc, L, nprod))
     return run_ptrans_cyclic(a, b, c, n, qs, lc, nq_total, l0, nprod, L, s);

@@ -196,3 +196,13 @@ def test_depth_0_with_few_products(drive, n, q, products, levels):
     for g in got:
         assert g["status"] == 0
         assert any("kara_split" in launch[0] for launch in g["launches"]) == levels
+
+
+# ---------------------------------------------------------------------------- one shared operand
+@pytest.mark.parametrize("q,channels,batch,tiles", [
+    (4194301, 1, 8, True), (4194301, 1, 511, True), (4194301, 1, 512, False), (4194301, 4, 127, True),
+    (4194301, 4, 128, False), (Q30, 1, 1, False),
+])
+def test_shared_operand_at_n_1024(drive, q, channels, batch, tiles):
+    got = drive([call("polymul_negacyclic_rns_shared", A, B, C, 1024, {"u32": [q] * channels}, channels, batch, None)])[0]
+    assert got["status"] == 0 and ("mfma32_shared" in got["launches"][0][0]) == tiles
