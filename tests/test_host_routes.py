@@ -206,3 +206,43 @@ def test_depth_0_with_few_products(drive, n, q, products, levels):
 def test_shared_operand_at_n_1024(drive, q, channels, batch, tiles):
     got = drive([call("polymul_negacyclic_rns_shared", A, B, C, 1024, {"u32": [q] * channels}, channels, batch, None)])[0]
     assert got["status"] == 0 and ("mfma32_shared" in got["launches"][0][0]) == tiles
+
+
+# -------------------------------------------------- the kernels that test_gpu_routes.py is about
+def launched(drive, calls):
+    got = drive(calls)
+    assert not any(g["status"] for g in got)
+    return [[launch[0] for launch in g["launches"]] for g in got]
+
+
+@pytest.mark.parametrize("n", [8192, 16384, 32768])
+def test_direct_64_bit_calls_stream(drive, n):
+    fns = ("polymul_negacyclic_u64", "polymul_cyclic_u64", "polymul_negacyclic_u64_shared")
+    for names in launched(drive, [call(fn, A, B, C, n, GOLDILOCKS, 2, None) for fn in fns]):
+        assert len(names) == 1 and "stream8_kernel" in names[0]
+
+
+def test_ten_channels_stream_in_two_launches(drive):
+    names, = launched(drive, [call("polymul_negacyclic_rns", A, B, C, 16384, {"u32": [Q30] * 10}, 10, 2, None)])
+    assert len(names) == 2 and all("stream_kernel" in k for k in names)
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+def test_tiles_beside_the_transform(drive, n):
+    for q in (3330, 1 << 20, Q30 - 1, (1 << 32) - 5):
+        shared, direct, cyclic = launched(drive, [call(fn, A, B, C, n, q, 5, None) for fn in (
+            "polymul_negacyclic_shared", "polymul_negacyclic", "polymul_cyclic")])
+        assert ["mfma32_shared_kernel" in shared[0], "mfma32_group_kernel" in direct[0],
+                "mfma32_group_kernel" in cyclic[0]] == [True] * 3
+
+
+def test_karatsuba_sub_products_and_library_scratch(drive):
+    qs = {"u32": [Q30 - 1, (1 << 32) - 5, 3329]}
+    calls = [call("polymul_negacyclic_rns_karatsuba", A, B, C, n, qs, 3, 3, depth, W, 1 << 30, None)
+             for n, depth in ((2048, 1), (4096, 1), (8192, 1), (4096, 2), (8192, 3))]
+    for names in launched(drive, calls):
+        assert "mfma32_group_kernel" in names[1]
+    small, outer = launched(drive, [call("polymul_negacyclic_rns_karatsuba_noalloc", A, B, C, n, {"u32": [Q30, 12289]}, 2, 3, 0, None)
+                                    for n in (4096, 16384)])
+    assert "ptrans_kernel" in small[0] and ["pt_outer_forward" in outer[0], "ptrans_kernel" in outer[1],
+                                            "pt_outer_inverse" in outer[2]] == [True] * 3
