@@ -184,8 +184,11 @@ __device__ __forceinline__ uint64_t pt_close(uint64_t x, uint64_t y, uint64_t q)
 }
 
 // (x, z) <- (x + Y z, Y z - x), Y = y^(16 R).  The difference is taken this way round
-// because the rotated operand of an addition or subtraction has to be its first one
-// (v_subrev_u32 with a DPP row rotation was measured to rotate the other operand).
+// because a rotated operand must not be what is subtracted: the compiler makes x - rot(z) one
+// v_subrev_u32 with the rotation on z, and on the GPU that gave rot(x) - z in all 64 lanes
+// (v_subrev_u32_dpp v1, v2, v1 row_ror:3 with x in v1 and z in v2, encoded as it stands there; ROCm 7.2).
+// x + rot(z) and rot(z) - x, v_add_u32 and v_sub_u32, were right in all of them.
+// tests/test_machine_code.py looks for reversed forms in the built library.
 template <int R, typename W>
 __device__ __forceinline__ void pt_butterfly(W& x, W& z, W q, uint32_t yhigh) {
   const W t = pt_shift<R>(z, q, yhigh);
