@@ -596,7 +596,7 @@ uint32_t ptrans_m(uint64_t n) { return n > 4096 ? 512 : 256; }
 
 // `points`: the transform's points, the outer one's included (their inverse goes into rc);
 // M: the sub-products' degree bound.
-bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points, uint32_t M) {
+void fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points, uint32_t M) {
   pm = PtMod32{};
   pm.m = make_mod32(q, L);
   uint32_t inv = q;  // Newton: doubles the correct low bits, three to begin with
@@ -610,7 +610,6 @@ bool fill_ptmod(PtMod32& pm, uint32_t q, int L, uint32_t points, uint32_t M) {
     pm.rc[s] = f > q / 2 ? (int32_t)((int64_t)f - q) : (int32_t)f;
     f = (f << 8) % q;
   }
-  return true;
 }
 // False when a constant of this modulus does not split into two signed words.
 bool fill_ptmod(PtMod64& pm, uint64_t q, int L, uint32_t points) {  // M = 256
@@ -1136,7 +1135,11 @@ std::atomic<uint32_t> g_plan_share_pct{140};
 std::atomic<uint32_t> g_plan_stream_pct{125};
 
 // A plan's 32-bit group goes through the polynomial transform where its calls would, at four limbs
-// (moduli above 2^24: the others' tiles do a quarter or half of the matrix work).  An item of
+// (moduli above 2^24).  Two and three would gain in plans with many of them (us on tiles and on the
+// transform inside this kernel: 1024 products of n = 4096 74 and 52, 128 and 60; 128 of 8192 122 and 37,
+// 127 and 42) but not in small ones (16 of 8192 23.1 and 25.9, 25.8 and 28.4; 40 of 2048 with 100 of 512
+// 26.4 and 28.7), and their code beside the four limbs' costs those 3 % (the uneven batch 36.9 and 38.0):
+// they stay on tiles.  An item of
 // 4096 / n products takes about as long as 5632 MFMAs of a tile group (20-26 us with a second
 // workgroup on its CU, where a group of n = 4096 with 8192 takes 38 us).  A product of n = 8192 is
 // three items, the sub-products of one Karatsuba level, and a share of the combine kernel: as
