@@ -947,20 +947,19 @@ polymul_status kara_workspace(uint64_t n, uint64_t products, uint32_t depth, uin
   return POLYMUL_OK;
 }
 
-// Calls of few products that depth 0 leaves to the built-in levels although the transform takes them,
-// us: n = 8192, whose transform has one workgroup per product, as long as the levels' 9 sub-products
-// of degree 2048, two per workgroup, find a CU each: one product 18.6 through the levels and 30.5
-// through the transform, 56 24.7 and 31.9, 60 31.8 and 32.0; with two limbs 15.0 and 19.2, 44 19.9 and
-// 20.0, 48 20.2 and 20.0.  n = 1024 at four limbs: two products 11.9 and 12.8, 192 13.4 and 13.7, 208 13.7
-// and 13.6.  At n = 2048 and 4096 one product takes 14.3 and 18.4 through them, 12.7 and 13.3 through it.
-bool kara_few(uint64_t n, int L, uint64_t products) {
-  return (n == 8192 && products <= (L == 2 ? 44 : 56)) || (n == 1024 && L == 4 && products <= 192);
-}
+// Calls of few products of n = 8192, whose transform has one workgroup per product: depth 0 leaves them to
+// the built-in levels as long as these' 9 sub-products of degree 2048, two per workgroup, find a CU each.
+// us: one product 18.6 through the levels and 30.5 through the transform, 56 24.7 and 31.9, 60 31.8 and
+// 32.0; with two limbs 15.0 and 19.2, 44 19.9 and 20.0, 48 20.2 and 20.0.  At n = 2048 and 4096 one
+// product takes 14.3 and 18.4 through the levels, 12.7 and 13.3 through the transform.  At n = 1024 it is the
+// transform too: 13.0 for two products and 13.7 for 192, where the levels' three launches keep the
+// caller's thread for 11 to 17.
+bool kara_few(uint64_t n, int L, uint64_t products) { return n == 8192 && products <= (L == 2 ? 44 : 56); }
 
 // The RNS Karatsuba route on validated arguments with a workspace of at least
 // kara_workspace(n, batch * L, depth, 4) bytes: split, sub-products, combine.  choose: the
-// depth is the library's to pick and nothing was tuned, so the transform goes first (its 4 n
-// words per product are within the 6.75 n of the two levels built in from n = 1024 on).
+// depth is the library's to pick and nothing was tuned, so the transform goes first, but for few products
+// of n = 8192 (its 4 n words per product are within the 6.75 n of the two levels built in from n = 1024 on).
 polymul_status run_rns_karatsuba(const uint32_t* a, const uint32_t* b, uint32_t* c, uint64_t n, const uint32_t* q,
                                  uint32_t L, uint64_t batch, uint32_t depth, bool choose, void* workspace,
                                  hipStream_t stream) {
