@@ -114,8 +114,9 @@ polymul_status polymul_negacyclic_plain(const uint32_t* a, const uint32_t* b, ui
  * large items along K into runs (items that would take more than an even share
  * of the work), the buffer the runs leave their residues in and the table of
  * the sums that one more launch forms from them; 32-bit groups of degree 8192 on
- * the polynomial transform use the same buffer for their sub-products, which one
- * launch per group puts together.  Pointers are baked in: later executes read
+ * the polynomial transform use the same buffer for their sub-products, at most 256
+ * MiB of it and none where that finds no room, which one launch per group puts
+ * together.  Pointers are baked in: later executes read
  * and write the same buffers.  A plan must not be executed concurrently with
  * itself.  flags: 0, or POLYMUL_PLAN_NO_GRAPH to launch directly each time.
  */
@@ -213,7 +214,8 @@ polymul_status polymul_negacyclic_u64_shared(const uint64_t* a, const uint64_t* 
  *                polymul_negacyclic_rns and the workspace is not used.  Where
  *                nothing is tuned and n >= 1024, moduli the polynomial transform
  *                takes (odd, at most 0x7F7F7F7F for 32-bit words) go through it
- *                instead of Karatsuba levels, in the same workspace.
+ *                instead of Karatsuba levels, in the same workspace; up to 56 products
+ *                of n = 8192 (44 where every modulus is at most 2^16) keep the levels.
  *   workspace:   device, 16-byte aligned, at least
  *                polymul_karatsuba_workspace_size(...) bytes, owned by the
  *                caller, not overlapping a, b or c; its contents on entry do
@@ -299,7 +301,8 @@ polymul_status polymul_negacyclic_rns_karatsuba_noalloc(const uint32_t* a, const
  * 64 <= n <= 512 (16x16 output tiles, v_mfma_i32_16x16x64_i8, the built-in
  * choice there).  t = 0 restores the built-in choice, which for n = 1024..8192 and
  * odd moduli is the polynomial transform instead of tiles of the whole product (both
- * rings; not at every limb count when n = 1024).  The table is process-wide;
+ * rings; not at every limb count when n = 1024, and not in plans of little work).  The get
+ * call returns the tile side, also where the transform runs.  The table is process-wide;
  * the autotuner (paper_2307_06554_amd/tune.py) times the candidates on the GPU
  * and calls polymul_tune_set with the winners.  Takes effect for launches and
  * plans created afterwards.  No HIP call is made.
@@ -332,7 +335,11 @@ polymul_status polymul_tune_param_get(uint32_t param, uint64_t* value);
  * of `products` products (batch * L for the RNS route, batch for the 64-bit
  * route; bucketed by floor(log2 products)), for 32-bit (elem_bytes 4) or 64-bit
  * (8) words.  depth 0 = the direct route, 1..3 = levels, 0xFF = back to the
- * built-in choice.  The get call returns the depth in force.  No HIP call.
+ * built-in choice.  The get call returns the entry, or the built-in number of levels
+ * where there is none: those run then only where the polynomial transform does not
+ * (see polymul_negacyclic_rns_karatsuba), so that giving that number back, here or as
+ * a call's depth, is not the same as leaving the choice at 0xFF and 0.  The table is
+ * for the Karatsuba calls alone.  No HIP call.
  * EINVAL: bad n, products, elem_bytes or depth.
  */
 polymul_status polymul_tune_set_karatsuba(uint64_t n, uint64_t products, uint32_t elem_bytes, uint32_t depth);

@@ -244,7 +244,8 @@ def _rns_through_workspace(name, a, b, c, n, qs, batch, stream):
 
 
 def polymul_negacyclic(a, b, q, out=None, stream=None):
-    """c = a*b in Z_q[x]/(x^n+1) for 32-bit words [..., n], q < 2^32 (int8-MFMA path)."""
+    """c = a*b in Z_q[x]/(x^n+1) for 32-bit words [..., n], q < 2^32 (int8-MFMA path).
+    n >= 16384, odd q <= 0x7F7F7F7F: with a workspace of 4 n words per product, at most 128 MiB of torch's memory."""
     n, batch = _pair(a, b)
     c = _result(out, a, 4)
     if n > 8192 and _rns_through_workspace("polymul_negacyclic", a, b, c, n, [int(q)], batch, stream):
@@ -266,7 +267,8 @@ def polymul_negacyclic_plain(a, b, q, out=None, stream=None):
 
 
 def polymul_negacyclic_u64(a, b, q, out=None, stream=None):
-    """c = a*b in Z_q[x]/(x^n+1) for 64-bit words [..., n], q < 2^64."""
+    """c = a*b in Z_q[x]/(x^n+1) for 64-bit words [..., n], q < 2^64.
+    n >= 8192, odd q: with a workspace of 4 n words per product, at most 128 MiB of torch's memory."""
     n, batch = _pair(a, b)
     c = _result(out, a, 8)
     if _large(n, batch, 8) and int(q) & 1:
@@ -302,11 +304,11 @@ def polymul_cyclic_u64(a, b, q, out=None, stream=None):
 
 
 def polymul_negacyclic_rns(a, b, qs, out=None, stream=None):
-    """RNS form: a, b are 32-bit words [batch, L, n]; channel l is taken mod qs[l]."""
+    """RNS form: a, b are 32-bit words [batch, L, n]; channel l is taken mod qs[l].
+    n >= 16384, odd moduli <= 0x7F7F7F7F: with a workspace as polymul_negacyclic."""
     batch, L, n = _rns_shape(a, b, qs)
     c = _result(out, a, 4)
-    if n > 8192 and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch,
-                                                  stream):
+    if n > 8192 and _rns_through_workspace("polymul_negacyclic_rns", a, b, c, n, [int(q) for q in qs], batch, stream):
         return c
     qarr = (ctypes.c_uint32 * L)(*[int(x) for x in qs])
     st = load_library().polymul_negacyclic_rns(_words(a, 4, "a"), _words(b, 4, "b"), _words(c, 4, "out"),
@@ -394,8 +396,8 @@ def polymul_karatsuba_workspace_size(n, L, batch, depth):
 
 
 def polymul_negacyclic_rns_karatsuba(a, b, qs, depth, workspace=None, out=None, stream=None):
-    """polymul_negacyclic_rns through `depth` Karatsuba levels.  workspace: a device
-    tensor of at least polymul_karatsuba_workspace_size bytes (allocated here if None)."""
+    """polymul_negacyclic_rns through `depth` Karatsuba levels (0: the tuned depth, or the
+    library's own choice, mostly the polynomial transform).  workspace: a device tensor of at least polymul_karatsuba_workspace_size bytes (allocated here if None)."""
     import torch
     batch, L, n = _rns_shape(a, b, qs)
     c = _result(out, a, 4)
@@ -496,12 +498,15 @@ def polymul_tune_param_get(name):
 
 
 def polymul_tune_set_karatsuba(n, products, elem_bytes, depth):
-    """Karatsuba depth that depth 0 resolves to for (n, products) and word size; 0xFF = built-in."""
+    """Karatsuba depth that depth 0 resolves to for (n, products) and word size; 0xFF = built-in,
+    the polynomial transform where it takes the moduli."""
     _check(load_library().polymul_tune_set_karatsuba(int(n), int(products), int(elem_bytes), int(depth)),
            "polymul_tune_set_karatsuba")
 
 
 def polymul_tune_get_karatsuba(n, products, elem_bytes):
+    """The table's entry, or the built-in number of levels where there is none (they run then
+    only where the polynomial transform does not)."""
     out = ctypes.c_uint32()
     _check(load_library().polymul_tune_get_karatsuba(int(n), int(products), int(elem_bytes), ctypes.byref(out)),
            "polymul_tune_get_karatsuba")
